@@ -308,20 +308,27 @@ struct CodecArgs {
   int n_cubes, n, levels;
   double step;
   const double* field;          // encode input
-  uint32_t* codes;              // [n_cubes][n^3] zigzag codes (workspace)
+  uint32_t* words;              // [n_cubes][n^3] packed words of each cube (workspace; a code has
+                                // at most 31 bits, so a cube's words never exceed n^3)
   uint8_t* widths;              // [n_cubes][n^3 / 32] group bit widths (workspace)
-  unsigned long long* sizes;    // [n_cubes] stream bytes of each cube (workspace)
-  unsigned long long* total;    // data bytes of the whole stream (workspace)
+  unsigned long long* sizes;    // [n_cubes] stream bytes of each cube, bit 63: a mark (workspace)
+  unsigned long long* result;   // data bytes of the whole stream, verdict (workspace)
   void* stream;                 // encode output
+  unsigned long long capacity;  // its size
   const void* stream_in;        // decode input
   unsigned long long data_bytes;  // decode: bytes after the header and offsets
   double* field_out;            // decode output
-  unsigned int* flags;          // bit 0: a code beyond 2^30; bit 1: a malformed cube stream
+  ScalarMirror* mirror;         // the result for the host, as spare[0..1]; nullptr: none
+  uint32_t seq;                 // written to mirror->seq after it
 };
+// Verdicts: a code beyond 2^30 or a value not finite; the buffer too small; not a stream of
+// this mesh; a malformed cube.
+constexpr unsigned long long kWcOver = 1, kWcFull = 2, kWcHeader = 4, kWcCube = 8;
 hipError_t launch_wc_encode(int NL, const CodecArgs& a, int grid, hipStream_t s);
 hipError_t launch_wc_header(const CodecArgs& a, hipStream_t s);
 hipError_t launch_wc_pack(int NL, const CodecArgs& a, int grid, hipStream_t s);
 hipError_t launch_wc_decode(int NL, const CodecArgs& a, int grid, hipStream_t s);
+hipError_t launch_wc_verdict(const CodecArgs& a, hipStream_t s);
 
 struct ScaleArgs {      // y = x * (vol ^ power) per cube (power = +1 or -1)
   const CubeMeta* meta;

@@ -1064,6 +1064,7 @@ size_t codec_cube_bound(int n) {
   const size_t G = size_t(n) * n * n / 32;
   return (G + 3) / 4 * 4 + 4 * 32 * G;
 }
+constexpr int kWcGrid = 1024;  // workgroups of the encoder and the decoder: four on each of 256 CUs
 int codec_levels(int n) { return n == 16 ? 4 : n == 8 ? 3 : 2; }
 
 CodecArgs codec_args(bcm_plan* P, double step) {
@@ -1072,12 +1073,26 @@ CodecArgs codec_args(bcm_plan* P, double step) {
   a.n = P->n;
   a.levels = codec_levels(P->n);
   a.step = step;
-  a.codes = P->at<uint32_t>(P->o_r);   // the Krylov vectors are free between solves
+  a.words = P->at<uint32_t>(P->o_r);   // the Krylov vectors are free between solves
   a.widths = P->at<uint8_t>(P->o_z);
   a.sizes = P->at<unsigned long long>(P->o_part[1]);
-  a.total = P->at<unsigned long long>(P->o_cflag);
-  a.flags = reinterpret_cast<unsigned int*>(P->at<char>(P->o_cflag) + 8);
+  a.result = P->at<unsigned long long>(P->o_cflag);
+  a.mirror = P->mirror;
+  a.seq = P->mirror ? ++P->mirror_seq : 0u;
   return a;
+}
+
+// Data bytes and verdict of the codec call in flight.
+int codec_result(bcm_plan* P, unsigned long long (&out)[2], hipStream_t s) {
+  if (P->mirror) {
+    Scalars sc;
+    if (int e = read_scalars(P, &sc, s)) return e;
+    std::memcpy(out, sc.spare, sizeof(out));
+    return BCM_OK;
+  }
+  HIPCHK(hipMemcpyAsync(out, P->at<char>(P->o_cflag), sizeof(out), hipMemcpyDeviceToHost, s), "codec readback");
+  HIPCHK(hipStreamSynchronize(s), "stream synchronize");
+  return BCM_OK;
 }
 
 // ---- no-allocation variant of the kinetic-energy objective --------------------------------
@@ -1673,26 +1688,24 @@ int bcm_compress(bcm_plan* P, const double* d_field, double step, void* d_stream
   CodecArgs a = codec_args(P, step);
   a.field = d_field;
   a.stream = d_stream;
-  const int grid = std::min(P->nc, 4096);
-  HIPCHK(launch_zero_u32(a.flags, s), "zero the codec flags");
-  HIPCHK(timed(P, cls_of("codec", 0), s, [&] { return launch_wc_encode(P->n, a, grid, s); }), "k_wc_encode");
+  a.capacity = capacity;
+  const int units = (P->nc + col_cpb(P->n) - 1) / col_cpb(P->n);
+  HIPCHK(timed(P, cls_of("codec", 0), s, [&] { return launch_wc_encode(P->n, a, std::min(units, kWcGrid), s); }),
+         "k_wc_encode");
   HIPCHK(launch_wc_header(a, s), "k_wc_header");
-  struct {
-    unsigned long long total;
-    unsigned int flags, pad;
-  } back{};
-  HIPCHK(hipMemcpyAsync(&back, a.total, sizeof(back), hipMemcpyDeviceToHost, s), "codec readback");
-  HIPCHK(hipStreamSynchronize(s), "stream synchronize");
-  if (back.flags & 1u) {
+  HIPCHK(timed(P, cls_of("codec", 0), s, [&] { return launch_wc_pack(P->n, a, std::min((P->nc + 3) / 4, 2048), s); }),
+         "k_wc_pack");
+  unsigned long long back[2];
+  if ((st = codec_result(P, back, s))) return st;
+  if (back[1] & kWcOver) {
     set_error("bcm_compress: step too small for the field (a code reaches 2^30) or a non-finite value");
     return BCM_ERR_INVALID_ARG;
   }
-  *bytes = head + size_t(back.total);
-  if (*bytes > capacity) {
+  *bytes = head + size_t(back[0]);
+  if (back[1] & kWcFull) {
     set_error("bcm_compress: stream buffer too small (the needed size is in *bytes)");
     return BCM_ERR_INVALID_ARG;
   }
-  HIPCHK(timed(P, cls_of("codec", 0), s, [&] { return launch_wc_pack(P->n, a, grid, s); }), "k_wc_pack");
   return BCM_OK;
 }
 
@@ -1713,33 +1726,22 @@ int bcm_decompress(bcm_plan* P, const void* d_stream, size_t bytes, double* d_fi
     return BCM_ERR_INVALID_ARG;
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  unsigned char h[32];
-  unsigned long long last = 0;
-  HIPCHK(hipMemcpyAsync(h, d_stream, 32, hipMemcpyDeviceToHost, s), "header readback");
-  HIPCHK(hipMemcpyAsync(&last, static_cast<const char*>(d_stream) + 32 + 8 * size_t(P->nc), 8,
-                        hipMemcpyDeviceToHost, s), "header readback");
-  HIPCHK(hipStreamSynchronize(s), "stream synchronize");
-  uint32_t hw[6];
-  double step = 0;
-  std::memcpy(hw, h, 24);
-  std::memcpy(&step, h + 24, 8);
-  if (hw[0] != 0x574D4342u || hw[1] != 1u || int(hw[2]) != P->nc || int(hw[3]) != P->n ||
-      int(hw[4]) != codec_levels(P->n) || !(step > 0) || !std::isfinite(step) || last != bytes - head) {
+  CodecArgs a = codec_args(P, 0.0);  // (the step comes from the stream)
+  a.stream_in = d_stream;
+  a.data_bytes = bytes - head;
+  a.field_out = d_field;
+  const int units = (P->nc + col_cpb(P->n) - 1) / col_cpb(P->n);
+  HIPCHK(timed(P, cls_of("codec", 0), s, [&] { return launch_wc_decode(P->n, a, std::min(units, kWcGrid), s); }),
+         "k_wc_decode");
+  HIPCHK(launch_wc_verdict(a, s), "k_wc_verdict");
+  unsigned long long back[2];
+  if ((st = codec_result(P, back, s))) return st;
+  if (back[1] & kWcHeader) {
     set_error("bcm_decompress: not a stream of this mesh (magic, version, cube count, n, levels, "
               "step or total size)");
     return BCM_ERR_INVALID_ARG;
   }
-  CodecArgs a = codec_args(P, step);
-  a.stream_in = d_stream;
-  a.data_bytes = bytes - head;
-  a.field_out = d_field;
-  HIPCHK(launch_zero_u32(a.flags, s), "zero the codec flags");
-  HIPCHK(timed(P, cls_of("codec", 0), s,
-               [&] { return launch_wc_decode(P->n, a, std::min(P->nc, 4096), s); }), "k_wc_decode");
-  unsigned int flags = 0;
-  HIPCHK(hipMemcpyAsync(&flags, a.flags, sizeof(flags), hipMemcpyDeviceToHost, s), "codec readback");
-  HIPCHK(hipStreamSynchronize(s), "stream synchronize");
-  if (flags & 2u) {
+  if (back[1] & kWcCube) {
     set_error("bcm_decompress: malformed cube stream(s); those cubes decode to zero");
     return BCM_ERR_INVALID_ARG;
   }
