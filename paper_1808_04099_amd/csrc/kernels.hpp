@@ -238,30 +238,25 @@ struct KineticArgs {    // sum_i V_i |u_i|^2 (partials per workgroup); g_u = gsc
   double* part;         // nullptr: no sum
 };
 
-// Momentum sub-step (kernels_mom.hip).  Two-layer face buffers: 12 n^2 values per cube and
-// component.
+// Momentum sub-step (kernels_mom.hip).  Face buffers: 4 n^2 values per cube and component.
 enum { MOM_EXPLICIT = 0, MOM_CN_START = 1, MOM_CN_ITER = 2 };
-
-template <typename TF>
-struct MomExportArgs {
-  int n_cubes;
-  const TF* x[3];
-  TF* xf[3];
-};
 
 template <typename TF>
 struct MomArgs {
   // MOM_EXPLICIT  out = v + dt (c1 H(v) + c2 hprev)                 (v = a = u^n)
-  // MOM_CN_START  rhs = v + dt/2 H(v); out = v + dt H(v); part: sum rhs^2   (v = a = u^n)
-  // MOM_CN_ITER   r = rhs + dt/2 H(v) - v; out = v + r / diag; part: sum r^2 (v = iterate)
-  // every mode: hout = H(v) (optional), outf = two-layer x faces of out (optional); vf / af:
-  // the x faces of v / a (their y and z halos are read from v / a themselves)
+  // MOM_CN_START  rhs = v + dt/2 H(v); out = v + dt H(v); part: sum rhs^2   (v = a = u^n);
+  //               outf = x faces of out, af = x faces of u^n's x component
+  // MOM_CN_ITER   r = rhs + dt/2 H(v) - v; out = v + r / diag; part: sum r^2 (v = iterate);
+  //               vf, af: x faces of v and of a's x component (read); outf: of out (written)
+  // (the y and z halos, and in the first two modes the x halo, are read from v / a themselves);
+  // hout = H(v) (optional; not in MOM_CN_ITER)
   const CubeMeta* meta;
+  const int32_t* launch;
   int n_cubes;
   const TF* v[3];
   const TF* vf[3];
   const TF* a[3];
-  const TF* af[3];
+  TF* af;
   const TF* hprev[3];
   TF* rhs[3];
   TF* out[3];
@@ -354,7 +349,6 @@ template <typename TF> hipError_t launch_adj_gp(int NL, const AdjGpArgs<TF>& a, 
 template <typename TF> hipError_t launch_adj_rhs(int NL, const AdjRhsArgs<TF>& a, hipStream_t s);
 hipError_t launch_scale(const ScaleArgs& a, hipStream_t s);
 template <typename TF> hipError_t launch_kinetic(const KineticArgs<TF>& a, int grid, hipStream_t s);
-template <typename TF> hipError_t launch_mom_export(int NL, const MomExportArgs<TF>& a, int grid, hipStream_t s);
 template <typename TF> hipError_t launch_ib_force(const IbArgs<TF>& a, hipStream_t s);
 hipError_t launch_zero_u32(unsigned int* p, hipStream_t s);
 template <typename TF> hipError_t launch_mom(int NL, int mode, const MomArgs<TF>& a, int grid, hipStream_t s);

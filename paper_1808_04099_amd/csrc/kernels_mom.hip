@@ -6,21 +6,29 @@
 // QUICK reaches two cells upwind, so the halo is two layers deep.  The y and z layers of a
 // neighbour are rows and planes of its cube (whole lines), read from the field itself, which
 // no pass writes while it is read (the iteration alternates between two arrays).  The x
-// layers (one value per row) go through a face buffer: per cube and component, faces f = 0, 1
-// (-x, +x), layers L = 0 (boundary layer) and 1 (next inside), NL^2 values each as [t2][t1]
-// (y, z).
-// Producers export it (k_mom_export for a caller's field, the iteration kernels for their own
-// output); consumers gather the neighbours' layers.  On a domain face
-// the two ghost layers mirror the cube's own two boundary layers: Dirichlet value g gives
-// 2 g - v, zero gradient gives v (inflow: every component Dirichlet, the normal one U_in into
-// the domain; slip: normal component Dirichlet 0, tangential zero gradient; open: zero
-// gradient).
+// layers are two values per row: the first pass of a step reads them from the caller's field,
+// the Crank-Nicolson sweeps from a face buffer that each pass writes for its own output (and
+// the first pass for the x component of u^n): per cube and component [face][k][j][2], the
+// cells i = 0, 1 of face 0 (-x) and i = n-2, n-1 of face 1 (+x), in the order of i.  On a
+// domain face the two ghost layers mirror the cube's own two boundary layers: Dirichlet value
+// g gives 2 g - v, zero gradient gives v (inflow: every component Dirichlet, the normal one
+// U_in into the domain; slip: normal component Dirichlet 0, tangential zero gradient; open:
+// zero gradient).
 //
-// Layout per workgroup as the column kernels: lane t owns column (i, j) of cube slot s
-// (CPB = 256 / NL^2 cubes per workgroup).  The cube is swept plane by plane: plane k of the
-// three components goes through LDS with a two-cell x/y ring, the z neighbours k-2..k+2 are
-// the lane's own column registers, and the x/y components of the advecting velocity of plane
-// k go through LDS with a one-cell ring.  Arithmetic is FP64 whatever the field type.
+// Layout: lane l of a cube's n^2 lanes owns column (i, j) and walks it plane by plane, with the
+// z neighbours k-2..k+2 in a register window and the flux through the lower z face carried up.
+// The x neighbours are other lanes of the same row of 16 lanes, fetched by DPP row shifts whose
+// out-of-row lanes take the halo values; the y neighbours go through LDS (two planes in turn,
+// one barrier a plane), where each lane also puts its share of the ring rows.  What plane k + 1
+// needs is loaded before plane k is computed.  Arithmetic is FP64 whatever the field type.
+//
+// What bounds it: HBM.  A Crank-Nicolson sweep of 33.5M cells in FP64 takes 0.76 ms and moves
+// 4.0 GB (96 bytes per cell are 3.2 GB; the rest is halo rows, planes and the face buffers),
+// 5.3 TB/s; the VALU is busy 330 us of it.  With every neighbour through LDS, two barriers a
+// plane and nothing loaded ahead it took 0.99 ms, and a separate export pass 0.2 ms a step.
+// Two waves a SIMD (about 250 registers): three spill 90 registers and take three times as
+// long; reading the y neighbours from memory instead of LDS keeps the L1 path busy 65% of the
+// time (0.98 ms).
 #include "kernels.hpp"
 #include "tile.hpp"
 
@@ -32,272 +40,314 @@ template <int NL>
 struct Mom {
   static constexpr int N2 = NL * NL, N3 = N2 * NL;
   static constexpr int CPB = NL >= 16 ? 1 : 256 / N2;
-  static constexpr int W4 = NL + 4, P4 = W4 * W4;  // plane with a two-cell ring
-  static constexpr int W2 = NL + 2, P2 = W2 * W2;  // plane with a one-cell ring
-  static constexpr int FS = 4 * N2;                // face-buffer values per cube and component
-  __device__ static int fidx(int f, int L, int t1, int t2) { return (f * 2 + L) * N2 + t2 * NL + t1; }
+  static constexpr int FS = 4 * N2;  // face-buffer values per cube and component
+  __device__ static int fidx(int f, int j, int q) { return (f * N2 + j) * 2 + q; }  // + 2 NL k
 };
 
-// Value across face f of a cube (kind kd) as an affine map of a source value: the
-// neighbour's layer (kd == FK_SAME: scale 1, shift 0) or the cube's own mirrored layer on a
-// domain face (Dirichlet g: -1, 2 g; zero gradient: 1, 0).
-struct Affine {
-  double scale, shift;
-};
-__device__ __forceinline__ Affine mom_rule(int kd, int f, int comp, double U_in) {
+// Value v of component comp mirrored across domain face f of kind kd.
+__device__ __forceinline__ double mom_ghost(double v, int kd, int f, int comp, double U_in) {
   const int d = f >> 1;
-  if (kd == FK_INFLOW) return {-1.0, 2.0 * (comp == d ? ((f & 1) ? -U_in : U_in) : 0.0)};
-  if (kd == FK_SLIP && comp == d) return {-1.0, 0.0};
-  return {1.0, 0.0};  // a neighbour, an open face, or a tangential component on a slip wall
+  if (kd == FK_INFLOW) return 2.0 * (comp == d ? ((f & 1) ? -U_in : U_in) : 0.0) - v;
+  if (kd == FK_SLIP && comp == d) return -v;
+  return v;  // an open face, or a tangential component on a slip wall
 }
 
-// Write the lane's share of the two-layer x faces of one component from its column x[0..NL-1].
-template <int NL, typename TF>
-__device__ __forceinline__ void mom_export_col(TF* mf, int c, const double (&x)[NL], int i, int j) {
-  using M = Mom<NL>;
-  TF* base = mf + (size_t)c * M::FS;
-#pragma unroll
-  for (int L = 0; L < 2; ++L) {
-    if (i == L)
-#pragma unroll
-      for (int k = 0; k < NL; ++k) base[M::fidx(0, L, j, k)] = TF(x[k]);
-    if (i == NL - 1 - L)
-#pragma unroll
-      for (int k = 0; k < NL; ++k) base[M::fidx(1, L, j, k)] = TF(x[k]);
+// v of the lane C (a DPP control) away, within the row of 16 lanes; `old` where there is none.
+template <int C>
+__device__ __forceinline__ double dpp64(double old, double v) {
+  const int lo = __builtin_amdgcn_update_dpp(__double2loint(old), __double2loint(v), C, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(__double2hiint(old), __double2hiint(v), C, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+constexpr int kRowShl = 0x100, kRowShr = 0x110;  // + distance: from the lane above / below
+
+// The cells i-2, i-1, i+1, i+2 of the lane's x line from its cell v and the halo value hx (on
+// lanes i = 0, 1: cells -2, -1; on i = n-2, n-1: cells n, n+1).
+template <int NL>
+__device__ __forceinline__ void x_line(double v, double hx, int i, double (&w)[5]) {
+  const double hm = dpp64<kRowShl + 1>(hx, hx), hp = dpp64<kRowShr + 1>(hx, hx);
+  w[2] = v;
+  if constexpr (NL == 16) {  // a line is a DPP row
+    w[0] = dpp64<kRowShr + 2>(hx, v);
+    w[1] = dpp64<kRowShr + 1>(hm, v);
+    w[3] = dpp64<kRowShl + 1>(hp, v);
+    w[4] = dpp64<kRowShl + 2>(hx, v);
+  } else {
+    const double m2 = dpp64<kRowShr + 2>(v, v), m1 = dpp64<kRowShr + 1>(v, v);
+    const double p1 = dpp64<kRowShl + 1>(v, v), p2 = dpp64<kRowShl + 2>(v, v);
+    w[0] = i < 2 ? hx : m2;
+    w[1] = i < 1 ? hm : m1;
+    w[3] = i > NL - 2 ? hp : p1;
+    w[4] = i > NL - 3 ? hx : p2;
   }
 }
 
-template <typename TF, int NL>
-__global__ __launch_bounds__(256) void k_mom_export(MomExportArgs<TF> a) {
-  using M = Mom<NL>;
-  const int t = threadIdx.x, s = t / M::N2, l = t - s * M::N2, i = l % NL, j = l / NL;
-  const int units = (a.n_cubes + M::CPB - 1) / M::CPB;
-  for (int u = blockIdx.x; u < units; u += gridDim.x) {
-    const int c = u * M::CPB + s;
-    if (s >= M::CPB || c >= a.n_cubes) continue;
-#pragma unroll
-    for (int comp = 0; comp < 3; ++comp) {
-      double x[NL];
-#pragma unroll
-      for (int k = 0; k < NL; ++k) x[k] = double(a.x[comp][(size_t)c * M::N3 + k * M::N2 + l]);
-      mom_export_col<NL, TF>(a.xf[comp], c, x, i, j);
-    }
-  }
+// QUICK value on the face between b and c of the line a, b, c, d, upwind on U.
+__device__ __forceinline__ double quick(double U, double a, double b, double c, double d) {
+  const bool pos = U >= 0.0;
+  const double near = pos ? b : c, next = pos ? c : b, far = pos ? a : d;
+  return 0.75 * near + 0.375 * next - 0.125 * far;
 }
 
-// One pass of H over every cube (see MomArgs for the modes).
-template <typename TF, int NL, int MODE>
+// What the lane reads for one plane besides its own column: the x halo value of each component,
+// the right-hand side (or previous H), its share of the y ring and, in a Crank-Nicolson sweep,
+// the advecting velocity's x component (own and halo) and y component.
+template <typename TF, int RN>
+struct MomPlane {
+  TF x[3], q[3], ring[RN], ax, hax, ay;
+};
+
+// One pass of H over every cube (see MomArgs for the modes).  OFF: the type of a byte offset
+// within one field (32 bits where the fields are below 4 GiB: a load is then a scalar base
+// plus one register).  NT: the output and a sweep's right-hand side bypass the caches.
+template <typename TF, int NL, int MODE, typename OFF, bool NT>
 __global__ __launch_bounds__(256, 2) void k_mom(MomArgs<TF> a) {
   using M = Mom<NL>;
-  __shared__ double pv[M::CPB][3][M::P4];
-  __shared__ double pa[M::CPB][2][M::P2];
+  constexpr bool ITER = MODE == MOM_CN_ITER;
+  constexpr int NA = ITER ? 4 : 3;            // arrays in LDS: v and, in a sweep, a_y
+  constexpr int PL = (NL + 4) * NL;           // one of their planes, with two ring rows a side
+  constexpr int RE = (ITER ? 14 : 12) * NL;   // ring values of a plane (a_y needs one row a side)
+  constexpr int RN = (RE + M::N2 - 1) / M::N2;
+  __shared__ double pl[2][M::CPB][NA][PL];    // planes k and k + 1 in turn: one barrier a plane
   __shared__ double red[8];
-  const int t = threadIdx.x, s = t / M::N2, l = t - s * M::N2, i = l % NL, j = l / NL;
-  const int units = (a.n_cubes + M::CPB - 1) / M::CPB;
+  const int t = threadIdx.x;
+  const int s = M::CPB == 1 ? 0 : t / M::N2, l = M::CPB == 1 ? t : t % M::N2, i = l % NL, j = l / NL;
+  const int units = col_units(M::CPB, a.n_cubes);
+  const bool xlo = i < 2, xhi = i >= NL - 2;  // lanes that hold x halo values
+  auto ld = [](const TF* p, OFF byte) { return *reinterpret_cast<const TF*>(reinterpret_cast<const char*>(p) + byte); };
+  auto ldn = [](const TF* p, OFF byte) { return ld_nt(reinterpret_cast<const TF*>(reinterpret_cast<const char*>(p) + byte)); };
+  constexpr OFF B = sizeof(TF);
   double acc = 0.0;
   for (int u = blockIdx.x; u < units; u += gridDim.x) {
-    const int c = u * M::CPB + s;
-    const bool live = c < a.n_cubes;
+    const int p = M::CPB == 1 ? u : ((u >> 3) * M::CPB + s) * 8 + (u & 7);
+    int c = p < a.n_cubes ? a.launch[p] : -1;
+    if (M::N2 >= 64) c = __builtin_amdgcn_readfirstlane(c);  // one cube per wavefront
+    const bool live = M::CPB == 1 || c >= 0;
     const int ce = live ? c : 0;
     const CubeMeta& m = a.meta[ce];
+    int kd[6], nb[6];  // face kinds; the cube across, or this one behind a domain face
+#pragma unroll
+    for (int f = 0; f < 6; ++f) {
+      kd[f] = m.kind[f];
+      nb[f] = kd[f] == FK_SAME ? m.nbr[f][0] : ce;
+      if (M::N2 >= 64) {
+        kd[f] = __builtin_amdgcn_readfirstlane(kd[f]);
+        nb[f] = __builtin_amdgcn_readfirstlane(nb[f]);
+      }
+    }
     const double ih = 1.0 / m.h, ih2 = ih * ih;
-    const size_t cb = (size_t)ce * M::N3 + l;
-    // Halo sources of this lane, each with the affine rule per component: the two layers
-    // across the -z / +z faces at (i, j), element offsets into the fields (the neighbour's
-    // planes NL-1, NL-2 / 0, 1; on a domain face the cube's own planes 0, 1 / NL-1, NL-2); and,
-    // for the ring lanes (rows j = 0..3 of the slot, face f = j), the two layers across face f
-    // at tangential position i, per plane k at ro + k * rs: for the x faces offsets into the
-    // face buffers (rs = NL), for the y faces into the fields (the neighbour's rows NL-1, NL-2
-    // / 0, 1, or the cube's own rows; rs = N2).
-    size_t zo[2][2], ro[2] = {0, 0};
-    Affine zr[2][4], rr[4];
+    const OFF own = ((OFF)ce * M::N3 + l) * B;
+    // the lane's ring values: array e / (4 NL), ring row e / NL % 4 (j = -2, -1, NL, NL + 1; of
+    // a_y only the inner two), cell e % NL
+    const TF* rp[RN];
+    int rdst[RN], rwall = 0;
 #pragma unroll
-    for (int side = 0; side < 2; ++side) {
-      const int f = 4 + side, kd = m.kind[f];
-      const bool nbr = kd == FK_SAME;
-      const size_t cube = nbr ? (size_t)m.nbr[f][0] : (size_t)ce;
-#pragma unroll
-      for (int L = 0; L < 2; ++L) {
-        // the layer L planes away from the shared face: the neighbour's far side, or this
-        // cube's own near side mirrored
-        const int plane = (side == 0) == nbr ? NL - 1 - L : L;
-        zo[side][L] = cube * M::N3 + (size_t)plane * M::N2 + j * NL + i;
-      }
-#pragma unroll
-      for (int comp = 0; comp < 3; ++comp) zr[side][comp] = nbr ? Affine{1.0, 0.0} : mom_rule(kd, f, comp, a.U_in);
+    for (int r = 0; r < RN; ++r) {
+      const int e = l + r * M::N2, arr = e / (4 * NL);
+      int q = e / NL % 4;
+      if (arr == 3) q += 1;  // rows NL * 12.. : j = -1 and NL
+      const int f = q < 2 ? 2 : 3, ii = e % NL;
+      const bool same = kd[f] == FK_SAME;
+      const int row = q < 2 ? (same ? NL - 2 + q : 1 - q) : (same ? q - 2 : NL + 1 - q);
+      const TF* base = arr == 0 ? a.v[0] : arr == 1 ? a.v[1] : arr == 2 ? a.v[2] : a.a[1];
+      rp[r] = base + (size_t)nb[f] * M::N3 + row * NL + ii;
+      rdst[r] = e < RE ? arr * PL + (q < 2 ? q : NL + q) * NL + ii : -1;
+      if (!same) rwall |= 1 << r;
     }
-    const bool ring = j < 4;
-    const int rf = j & 3, rd = rf >> 1, rside = rf & 1;
-    const bool ry = rf >= 2;  // a y face: rows of the fields
-    const size_t rs = ry ? M::N2 : NL;
-    {
-      const int kd = m.kind[rf];
-      const bool nbr = kd == FK_SAME;
-      const size_t cube = nbr ? (size_t)m.nbr[rf][0] : (size_t)ce;
-      const int fs = nbr ? rf ^ 1 : rf;
-#pragma unroll
-      for (int L = 0; L < 2; ++L) {
-        const int row = (rside == 0) == nbr ? NL - 1 - L : L;
-        ro[L] = ry ? cube * M::N3 + (size_t)row * NL + i : cube * M::FS + M::fidx(fs, L, i, 0);
-      }
-#pragma unroll
-      for (int comp = 0; comp < 3; ++comp) rr[comp] = nbr ? Affine{1.0, 0.0} : mom_rule(kd, rf, comp, a.U_in);
-    }
-    // z stencil windows of the lane's column, rotated plane by plane: v at k-2..k+2 (wv) and
-    // a_z at k-1..k+1 (za); gh holds the two planes past the +z face
-    double gh[3][2], wv[3][5], za[3];
-#pragma unroll
-    for (int comp = 0; comp < 3; ++comp) {
-#pragma unroll
-      for (int L = 0; L < 2; ++L) {
-        gh[comp][L] = zr[1][comp].scale * double(a.v[comp][zo[1][L]]) + zr[1][comp].shift;
-        wv[comp][1 - L] = zr[0][comp].scale * double(a.v[comp][zo[0][L]]) + zr[0][comp].shift;
-      }
-      wv[comp][2] = double(a.v[comp][cb]);
-      wv[comp][3] = double(a.v[comp][cb + M::N2]);
-      wv[comp][4] = double(a.v[comp][cb + 2 * M::N2]);
-    }
-    const double azh = zr[1][2].scale * double(a.a[2][zo[1][0]]) + zr[1][2].shift;
-    za[0] = zr[0][2].scale * double(a.a[2][zo[0][0]]) + zr[0][2].shift;
-    za[1] = double(a.a[2][cb]);
-    za[2] = double(a.a[2][cb + M::N2]);
-    const int rpos0 = rside ? NL + 2 : 1, rpos1 = rside ? NL + 3 : 0;  // ring index along rd
-    const int ridx0 = rd == 0 ? (i + 2) * M::W4 + rpos0 : rpos0 * M::W4 + i + 2;
-    const int ridx1 = rd == 0 ? (i + 2) * M::W4 + rpos1 : rpos1 * M::W4 + i + 2;
-    const int rp = rside ? NL + 1 : 0;
-    const int ria = rd == 0 ? (i + 1) * M::W2 + rp : rp * M::W2 + i + 1;
-    const Affine ra = rd == 0 ? rr[0] : rr[1];  // a select: a dynamic index would put rr in scratch
-    // The outputs of plane k are stored at the top of plane k + 1, after that plane's loads
-    // are issued: the vector-memory counter is in order, so a load issued after a store could
-    // not be consumed before the store completes.
-    double po[3] = {0.0, 0.0, 0.0}, ph[3] = {0.0, 0.0, 0.0};
-    auto put = [&](int kp) __attribute__((always_inline)) {
-      if (!live) return;
-      const size_t gp = cb + (size_t)kp * M::N2;
+    const bool xwall = (xlo && kd[0] != FK_SAME) || (xhi && kd[1] != FK_SAME);
+    const int xf = xlo ? 0 : 1, xk = xlo ? kd[0] : kd[1];
+    // x halo of the lane's row (lanes xlo, xhi; the others read a value that is not used): the
+    // neighbour's cell, or this cube's mirrored one; in the field and in the face buffers
+    const int xcube = xlo ? nb[0] : nb[1];
+    const int xcell = xlo ? (xwall ? 1 - i : NL - 2 + i) : xhi ? (xwall ? 2 * NL - 3 - i : i - (NL - 2)) : 0;
+    const int side = xwall ? xf : 1 - xf;
+    const OFF xo = ITER ? ((OFF)xcube * M::FS + M::fidx(side, j, xlo || xhi ? xcell - (side ? NL - 2 : 0) : 0)) * B
+                        : ((OFF)xcube * M::N3 + j * NL + xcell) * B;
+    const OFF fb = ((OFF)ce * M::FS + M::fidx(xf, j, xlo ? i : i - (NL - 2))) * B;  // the lane's own cell there
+    // z windows of the lane's column, rotated plane by plane: v at k-2..k+2 and a_z at k-1..k+1.
+    // Byte offset of plane k of the column, -2 <= k < NL + 2 (behind a wall: of its mirror)
+    auto plane = [&](int k) -> OFF {
+      const int kl = kd[4] == FK_SAME ? k + NL : -1 - k, kh = kd[5] == FK_SAME ? k - NL : 2 * NL - 1 - k;
+      const int cube = k < 0 ? nb[4] : k < NL ? ce : nb[5], kk = k < 0 ? kl : k < NL ? k : kh;
+      return ((OFF)cube * M::N3 + kk * M::N2 + l) * B;
+    };
+    const bool zwall_lo = kd[4] != FK_SAME, zwall_hi = kd[5] != FK_SAME;
+    using In = MomPlane<TF, RN>;
+    auto fetch = [&](In& in, int k) __attribute__((always_inline)) {
 #pragma unroll
       for (int comp = 0; comp < 3; ++comp) {
-        const double o = po[comp];
-        a.out[comp][gp] = TF(o);
-        if (a.hout[comp]) a.hout[comp][gp] = TF(ph[comp]);
-        if (a.outf[comp]) {  // two-layer x faces of the output, cell by cell
-          TF* fb = a.outf[comp] + (size_t)c * M::FS;
+        in.x[comp] = ITER ? ld(a.vf[comp] + k * (2 * NL), xo) : ld(a.v[comp] + k * M::N2, xo);
+        in.q[comp] = TF(0);
+        if (ITER) in.q[comp] = NT ? ldn(a.rhs[comp] + k * M::N2, own) : ld(a.rhs[comp] + k * M::N2, own);
+        if (MODE == MOM_EXPLICIT && a.hprev[comp]) in.q[comp] = ld(a.hprev[comp] + k * M::N2, own);
+      }
 #pragma unroll
-          for (int L = 0; L < 2; ++L) {
-            if (i == L) fb[M::fidx(0, L, j, kp)] = TF(o);
-            if (i == NL - 1 - L) fb[M::fidx(1, L, j, kp)] = TF(o);
-          }
-        }
+      for (int r = 0; r < RN; ++r) in.ring[r] = rp[r][k * M::N2];
+      if (ITER) {
+        in.ax = ld(a.a[0] + k * M::N2, own);
+        in.hax = ld(a.af + k * (2 * NL), xo);
+        in.ay = ld(a.a[1] + k * M::N2, own);
       }
     };
-#pragma unroll 1
-    for (int k = 0; k < NL; ++k) {
-      const double axk = double(a.a[0][cb + k * M::N2]), ayk = double(a.a[1][cb + k * M::N2]);
-      double qk[3];  // right-hand side (or previous H) of plane k
+    double wv[3][5], za[3], fz[3];
+    In cur;
+    {
+      TF wr[3][5], zr[3];
+#pragma unroll
+      for (int q = 0; q < 5; ++q) {
+        const OFF o = plane(q - 2);
+#pragma unroll
+        for (int comp = 0; comp < 3; ++comp) wr[comp][q] = ld(a.v[comp], o);
+        if (ITER && q > 0 && q < 4) zr[q - 1] = ld(a.a[2], o);
+      }
+      fetch(cur, 0);
 #pragma unroll
       for (int comp = 0; comp < 3; ++comp) {
-        qk[comp] = 0.0;
-        if (MODE == MOM_CN_ITER) qk[comp] = double(a.rhs[comp][cb + k * M::N2]);
-        if (MODE == MOM_EXPLICIT && a.hprev[comp]) qk[comp] = double(a.hprev[comp][cb + k * M::N2]);
-      }
-      TF rgv[7];
-      if (ring) {
-        const size_t ko = (size_t)k * rs;
 #pragma unroll
-        for (int comp = 0; comp < 3; ++comp) {
-          const TF* src = ry ? a.v[comp] : a.vf[comp];
-          rgv[2 * comp] = src[ro[0] + ko];
-          rgv[2 * comp + 1] = src[ro[1] + ko];
+        for (int q = 0; q < 5; ++q) {
+          wv[comp][q] = double(wr[comp][q]);
+          if (q < 2 && zwall_lo) wv[comp][q] = mom_ghost(wv[comp][q], kd[4], 4, comp, a.U_in);
         }
-        rgv[6] = (ry ? a.a[rd] : a.af[rd])[ro[0] + ko];
       }
+#pragma unroll
+      for (int q = 0; q < 3; ++q) za[q] = ITER ? double(zr[q]) : wv[2][q + 1];
+      if (ITER && zwall_lo) za[0] = mom_ghost(za[0], kd[4], 4, 2, a.U_in);
+    }
+    {
+      const double U = 0.5 * (za[0] + za[1]);  // flux through the -z face, carried upwards
+#pragma unroll
+      for (int comp = 0; comp < 3; ++comp) fz[comp] = U * quick(U, wv[comp][0], wv[comp][1], wv[comp][2], wv[comp][3]);
+    }
+    double po[3] = {0.0, 0.0, 0.0}, ph[3] = {0.0, 0.0, 0.0}, pr[3] = {0.0, 0.0, 0.0}, pa = 0.0;
+    auto put = [&](int kp) __attribute__((always_inline)) {
+      if (!live) return;
+      auto st = [](TF* p, OFF byte, double v) { *reinterpret_cast<TF*>(reinterpret_cast<char*>(p) + byte) = TF(v); };
+      auto stn = [](TF* p, OFF byte, double v) { st_nt(reinterpret_cast<TF*>(reinterpret_cast<char*>(p) + byte), TF(v)); };
+#pragma unroll
+      for (int comp = 0; comp < 3; ++comp) {
+        if (NT) stn(a.out[comp] + kp * M::N2, own, po[comp]);
+        else st(a.out[comp] + kp * M::N2, own, po[comp]);
+        if (MODE == MOM_CN_START) st(a.rhs[comp] + kp * M::N2, own, pr[comp]);
+        if (!ITER && a.hout[comp]) st(a.hout[comp] + kp * M::N2, own, ph[comp]);
+      }
+      if (MODE != MOM_EXPLICIT && (xlo || xhi)) {
+#pragma unroll
+        for (int comp = 0; comp < 3; ++comp) st(a.outf[comp] + kp * (2 * NL), fb, po[comp]);
+        if (!ITER) st(a.af + kp * (2 * NL), fb, pa);
+      }
+    };
+    // Plane k: the outputs of plane k - 1 are stored, the loads of plane k + 1 issued, and
+    // plane k is computed from what was loaded a plane before (the vector-memory counter is in
+    // order: a load issued after a store is not consumed before the store completes).
+    auto step = [&](const In& in, In& next, int k, int buf) __attribute__((always_inline)) {
       if (k > 0) put(k - 1);
-      // plane k into LDS: interior, then the rings
+      TF nv[3], naz = TF(0);
+      {
+        const OFF o3 = plane(k + 3 <= NL + 1 ? k + 3 : NL + 1);  // (past the last one: not used)
 #pragma unroll
-      for (int comp = 0; comp < 3; ++comp) pv[s][comp][(j + 2) * M::W4 + i + 2] = wv[comp][2];
-      pa[s][0][(j + 1) * M::W2 + i + 1] = axk;
-      pa[s][1][(j + 1) * M::W2 + i + 1] = ayk;
-      if (ring) {
-#pragma unroll
-        for (int comp = 0; comp < 3; ++comp) {
-          pv[s][comp][ridx0] = rr[comp].scale * double(rgv[2 * comp]) + rr[comp].shift;
-          pv[s][comp][ridx1] = rr[comp].scale * double(rgv[2 * comp + 1]) + rr[comp].shift;
-        }
-        pa[s][rd][ria] = ra.scale * double(rgv[6]) + ra.shift;
+        for (int comp = 0; comp < 3; ++comp) nv[comp] = ld(a.v[comp], o3);
+        if (ITER) naz = ld(a.a[2], plane(k + 2));
       }
+      if (k + 1 < NL) fetch(next, k + 1);
+      double* y = &pl[buf][s][0][0];
+      const int at = (j + 2) * NL + i;
+#pragma unroll
+      for (int comp = 0; comp < 3; ++comp) y[comp * PL + at] = wv[comp][2];
+      const double ay1 = ITER ? double(in.ay) : wv[1][2];
+      if (ITER) y[3 * PL + at] = ay1;
+#pragma unroll
+      for (int r = 0; r < RN; ++r) {
+        double v = double(in.ring[r]);
+        if (rwall >> r & 1) {
+          const int e = l + r * M::N2, arr = e / (4 * NL), q = e / NL % 4 + (arr == 3 ? 1 : 0);
+          v = mom_ghost(v, q < 2 ? kd[2] : kd[3], q < 2 ? 2 : 3, arr == 3 ? 1 : arr, a.U_in);
+        }
+        if (RE % M::N2 == 0 || rdst[r] >= 0) y[rdst[r]] = v;
+      }
+      double hx[3], hax = double(in.hax);
+#pragma unroll
+      for (int comp = 0; comp < 3; ++comp) hx[comp] = double(in.x[comp]);
+      if (xwall) {
+#pragma unroll
+        for (int comp = 0; comp < 3; ++comp) hx[comp] = mom_ghost(hx[comp], xk, xf, comp, a.U_in);
+        if (ITER) hax = mom_ghost(hax, xk, xf, 0, a.U_in);
+      }
+      double xa[5];
+      x_line<NL>(ITER ? double(in.ax) : wv[0][2], ITER ? hax : hx[0], i, xa);
       __syncthreads();
-      const double Ux[2] = {0.5 * (pa[s][0][(j + 1) * M::W2 + i] + axk),
-                            0.5 * (axk + pa[s][0][(j + 1) * M::W2 + i + 2])};
-      const double Uy[2] = {0.5 * (pa[s][1][j * M::W2 + i + 1] + ayk),
-                            0.5 * (ayk + pa[s][1][(j + 2) * M::W2 + i + 1])};
+      const int ya = (ITER ? 3 : 1) * PL + at;
+      const double Ux[2] = {0.5 * (xa[1] + xa[2]), 0.5 * (xa[2] + xa[3])};
+      const double Uy[2] = {0.5 * (y[ya - NL] + ay1), 0.5 * (ay1 + y[ya + NL])};
       const double Uz[2] = {0.5 * (za[0] + za[1]), 0.5 * (za[1] + za[2])};
       // interior Jacobi diagonal of H (Crank-Nicolson iterations): the coefficient of v(i)
       // in the two QUICK face values of each axis, and the diffusion's -6 nu / h^2
-      double dg = 0.0;
-      if (MODE == MOM_CN_ITER) {
+      double inv_diag = 0.0;
+      if (ITER) {
+        double dg = 0.0;  // Up (Up >= 0 ? 3/4 : 3/8) - Um (Um >= 0 ? 3/8 : 3/4) per axis
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
           const double Um = d == 0 ? Ux[0] : d == 1 ? Uy[0] : Uz[0];
           const double Up = d == 0 ? Ux[1] : d == 1 ? Uy[1] : Uz[1];
-          dg += (Up * (Up >= 0.0 ? 0.75 : 0.375) - Um * (Um >= 0.0 ? 0.375 : 0.75)) * ih;
+          dg += 0.5625 * (Up - Um) + 0.1875 * (fabs(Up) + fabs(Um));
         }
+        dg *= ih;
+        inv_diag = 1.0 / fmax(1.0 + 0.5 * a.dt * (6.0 * a.nu * ih2 + dg), 0.5);
       }
-      const size_t g = cb + k * M::N2;
 #pragma unroll
       for (int comp = 0; comp < 3; ++comp) {
-        double H = 0.0;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          double w[5];
-#pragma unroll
-          for (int o = -2; o <= 2; ++o) {
-            if (d == 0) w[o + 2] = pv[s][comp][(j + 2) * M::W4 + i + 2 + o];
-            else if (d == 1) w[o + 2] = pv[s][comp][(j + 2 + o) * M::W4 + i + 2];
-            else w[o + 2] = wv[comp][o + 2];
-          }
-          const double Um = d == 0 ? Ux[0] : d == 1 ? Uy[0] : Uz[0];
-          const double Up = d == 0 ? Ux[1] : d == 1 ? Uy[1] : Uz[1];
-          const double qp = Up >= 0.0 ? 0.75 * w[2] + 0.375 * w[3] - 0.125 * w[1]
-                                      : 0.75 * w[3] + 0.375 * w[2] - 0.125 * w[4];
-          const double qm = Um >= 0.0 ? 0.75 * w[1] + 0.375 * w[2] - 0.125 * w[0]
-                                      : 0.75 * w[2] + 0.375 * w[1] - 0.125 * w[3];
-          H += a.nu * ((w[3] - 2.0 * w[2] + w[1]) * ih2) - (Up * qp - Um * qm) * ih;
-        }
+        double w[5], H;
         const double v0 = wv[comp][2];
-        double o;
+        const double* yc = y + comp * PL + at;
+        const double y0 = yc[-2 * NL], y1 = yc[-NL], y3 = yc[NL], y4 = yc[2 * NL];
+        x_line<NL>(v0, hx[comp], i, w);
+        H = a.nu * ((w[3] - 2.0 * v0 + w[1]) * ih2) -
+            (Ux[1] * quick(Ux[1], w[1], v0, w[3], w[4]) - Ux[0] * quick(Ux[0], w[0], w[1], v0, w[3])) * ih;
+        H += a.nu * ((y3 - 2.0 * v0 + y1) * ih2) -
+             (Uy[1] * quick(Uy[1], y1, v0, y3, y4) - Uy[0] * quick(Uy[0], y0, y1, v0, y3)) * ih;
+        const double* z = wv[comp];
+        const double up = Uz[1] * quick(Uz[1], z[1], v0, z[3], z[4]);
+        H += a.nu * ((z[3] - 2.0 * v0 + z[1]) * ih2) - (up - fz[comp]) * ih;
+        fz[comp] = up;
         if (MODE == MOM_EXPLICIT) {
-          o = v0 + a.dt * (a.c1 * H + a.c2 * qk[comp]);
+          po[comp] = v0 + a.dt * (a.c1 * H + a.c2 * double(in.q[comp]));
         } else if (MODE == MOM_CN_START) {
-          const double rhs = v0 + 0.5 * a.dt * H;
-          if (live) a.rhs[comp][g] = TF(rhs);
-          acc += rhs * rhs;
-          o = v0 + a.dt * H;  // Euler predictor as the first iterate
+          pr[comp] = v0 + 0.5 * a.dt * H;
+          if (live) acc += pr[comp] * pr[comp];
+          po[comp] = v0 + a.dt * H;  // Euler predictor as the first iterate
         } else {
-          const double diag = fmax(1.0 + 0.5 * a.dt * (6.0 * a.nu * ih2 + dg), 0.5);
-          const double r = qk[comp] + 0.5 * a.dt * H - v0;
-          acc += r * r;
-          o = v0 + r / diag;
+          const double r = double(in.q[comp]) + 0.5 * a.dt * H - v0;
+          if (live) acc += r * r;
+          po[comp] = v0 + r * inv_diag;
         }
-        po[comp] = o;
         ph[comp] = H;
       }
-      __syncthreads();  // the next plane overwrites the LDS planes
-      // rotate the z windows; the plane entering at k + 3 is the cube's, or a ghost plane
-      const int kn = k + 3;
-      const int kl = kn < NL ? kn : NL - 1;  // clamped: always an address inside the cube
+      pa = wv[0][2];
 #pragma unroll
       for (int comp = 0; comp < 3; ++comp) {
-        const double nv = double(a.v[comp][cb + kl * M::N2]);
-        wv[comp][0] = wv[comp][1];
-        wv[comp][1] = wv[comp][2];
-        wv[comp][2] = wv[comp][3];
-        wv[comp][3] = wv[comp][4];
-        wv[comp][4] = kn < NL ? nv : (kn == NL ? gh[comp][0] : gh[comp][1]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) wv[comp][q] = wv[comp][q + 1];
+        wv[comp][4] = double(nv[comp]);
       }
-      const int ka = k + 2 < NL ? k + 2 : NL - 1;
-      const double na = double(a.a[2][cb + ka * M::N2]);
-      za[0] = za[1];
-      za[1] = za[2];
-      za[2] = k + 2 < NL ? na : azh;
+      if (ITER) {
+        za[0] = za[1];
+        za[1] = za[2];
+        za[2] = double(naz);
+      }
+      if (zwall_hi && k + 3 >= NL) {
+#pragma unroll
+        for (int comp = 0; comp < 3; ++comp) wv[comp][4] = mom_ghost(wv[comp][4], kd[5], 5, comp, a.U_in);
+        if (ITER && k + 2 >= NL) za[2] = mom_ghost(za[2], kd[5], 5, 2, a.U_in);
+      }
+      if (!ITER) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) za[q] = wv[2][q + 1];
+      }
+    };
+#pragma unroll 1
+    for (int k = 0; k < NL; k += 2) {
+      In alt;
+      step(cur, alt, k, 0);
+      step(alt, cur, k + 1, 1);
     }
     put(NL - 1);
   }
@@ -317,23 +367,17 @@ __global__ __launch_bounds__(256, 2) void k_mom(MomArgs<TF> a) {
     default: return hipErrorInvalidValue;             \
   }
 
-template <typename TF>
-hipError_t launch_mom_export(int NL, const MomExportArgs<TF>& a, int grid, hipStream_t s) {
-  BCM_MOM_NL(NL, hipLaunchKernelGGL((k_mom_export<TF, NLC>), dim3(grid), dim3(256), 0, s, a));
-  return hipGetLastError();
-}
-
-template <typename TF>
-hipError_t launch_mom(int NL, int mode, const MomArgs<TF>& a, int grid, hipStream_t s) {
+template <typename TF, typename OFF, bool NT>
+static hipError_t launch_mom_as(int NL, int mode, const MomArgs<TF>& a, int grid, hipStream_t s) {
   switch (mode) {
     case MOM_EXPLICIT:
-      BCM_MOM_NL(NL, hipLaunchKernelGGL((k_mom<TF, NLC, MOM_EXPLICIT>), dim3(grid), dim3(256), 0, s, a));
+      BCM_MOM_NL(NL, hipLaunchKernelGGL((k_mom<TF, NLC, MOM_EXPLICIT, OFF, NT>), dim3(grid), dim3(256), 0, s, a));
       break;
     case MOM_CN_START:
-      BCM_MOM_NL(NL, hipLaunchKernelGGL((k_mom<TF, NLC, MOM_CN_START>), dim3(grid), dim3(256), 0, s, a));
+      BCM_MOM_NL(NL, hipLaunchKernelGGL((k_mom<TF, NLC, MOM_CN_START, OFF, NT>), dim3(grid), dim3(256), 0, s, a));
       break;
     case MOM_CN_ITER:
-      BCM_MOM_NL(NL, hipLaunchKernelGGL((k_mom<TF, NLC, MOM_CN_ITER>), dim3(grid), dim3(256), 0, s, a));
+      BCM_MOM_NL(NL, hipLaunchKernelGGL((k_mom<TF, NLC, MOM_CN_ITER, OFF, NT>), dim3(grid), dim3(256), 0, s, a));
       break;
     default:
       return hipErrorInvalidValue;
@@ -341,8 +385,19 @@ hipError_t launch_mom(int NL, int mode, const MomArgs<TF>& a, int grid, hipStrea
   return hipGetLastError();
 }
 
-template hipError_t launch_mom_export<float>(int, const MomExportArgs<float>&, int, hipStream_t);
-template hipError_t launch_mom_export<double>(int, const MomExportArgs<double>&, int, hipStream_t);
+template <typename TF>
+hipError_t launch_mom(int NL, int mode, const MomArgs<TF>& a, int grid, hipStream_t s) {
+  const size_t field = size_t(a.n_cubes) * NL * NL * NL * sizeof(TF);
+  // 32-bit byte offsets of cells and of face-buffer entries (at most one per cell)
+  const bool small = field <= 0xFFFFFFFFull;
+  // streamed once a sweep's twelve words per cell exceed the 256 MB last-level cache (33.5M
+  // cells in FP64: 13.9 -> 13.6 ms a Crank-Nicolson step; 2M cells in FP32, which fit: 45 us
+  // an AB2 step against 50 streamed)
+  if (!small) return launch_mom_as<TF, size_t, true>(NL, mode, a, grid, s);
+  if (12 * field > (size_t(256) << 20)) return launch_mom_as<TF, uint32_t, true>(NL, mode, a, grid, s);
+  return launch_mom_as<TF, uint32_t, false>(NL, mode, a, grid, s);
+}
+
 template hipError_t launch_mom<float>(int, int, const MomArgs<float>&, int, hipStream_t);
 template hipError_t launch_mom<double>(int, int, const MomArgs<double>&, int, hipStream_t);
 

@@ -81,9 +81,9 @@ struct bcm_plan {
   // workspace offsets
   size_t o_meta = 0, o_launch = 0, o_part[3] = {0, 0, 0}, o_sc = 0, o_cw = 0;
   size_t o_nb27 = 0;  // 27-neighbourhoods (trilinear prolongation), 0 = not used
-  // momentum sub-step (single-level meshes with n >= 4, else 0): two-layer faces of u^n and of
-  // the two Crank-Nicolson iterates, its right-hand side and a second iterate
-  size_t o_mfa[3] = {0, 0, 0}, o_mfv[2][3] = {{0, 0, 0}, {0, 0, 0}}, o_mrhs[3] = {0, 0, 0},
+  // momentum sub-step (single-level meshes with n >= 4, else 0): x faces of u^n's x component
+  // and of the two Crank-Nicolson iterates, its right-hand side and a second iterate
+  size_t o_mfa = 0, o_mfv[2][3] = {{0, 0, 0}, {0, 0, 0}}, o_mrhs[3] = {0, 0, 0},
          o_mit[3] = {0, 0, 0};
   bool momentum = false;
   // Lagrangian-particle forcing: per-level point-location tables (finest level first)
@@ -904,31 +904,25 @@ int kinetic_impl(bcm_plan* P, const void* const u[3], double rho, double g_scale
   return BCM_OK;
 }
 
-// Momentum sub-step (Eq. (substep1)): export the two-layer faces of u^n, then one explicit pass
-// (Euler, AB2) or the Crank-Nicolson start and its Jacobi iterations, which alternate between
-// the caller's output and the plan's second iterate.
+constexpr int kMomGrid = 2048;
+
+// Momentum sub-step (Eq. (substep1)): one explicit pass (Euler, AB2), or the Crank-Nicolson
+// start and its Jacobi iterations, which alternate between the caller's output and the plan's
+// second iterate.
 template <typename TF>
 int momentum_impl(bcm_plan* P, const bcm_momentum_in* in, bcm_momentum_out* out, bcm_report* rep,
                   hipStream_t s) {
   const int NL = P->n, nc = P->nc;
-  const int units = nc;  // cubes or groups of cubes; the grid never exceeds the partial buffers
-  const int grid = std::min(units, 2048);
-  MomExportArgs<TF> ea{};
-  ea.n_cubes = nc;
-  for (int d = 0; d < 3; ++d) {
-    ea.x[d] = static_cast<const TF*>(in->u[d]);
-    ea.xf[d] = P->at<TF>(P->o_mfa[d]);
-  }
-  HIPCHK(timed(P, cls_of("momentum_start", 0), s, [&] { return launch_mom_export<TF>(NL, ea, grid, s); }),
-         "k_mom_export");
+  // (a multiple of 8 or every unit: a workgroup keeps to its XCD's stretch of the launch table)
+  const int grid = std::min(col_units(col_cpb(NL), nc), kMomGrid);
   MomArgs<TF> ma{};
   ma.meta = P->at<const CubeMeta>(P->o_meta);
+  ma.launch = P->at<const int32_t>(P->o_launch);
   ma.n_cubes = nc;
+  ma.af = P->at<TF>(P->o_mfa);
   for (int d = 0; d < 3; ++d) {
     ma.v[d] = static_cast<const TF*>(in->u[d]);
-    ma.vf[d] = P->at<const TF>(P->o_mfa[d]);
     ma.a[d] = static_cast<const TF*>(in->u[d]);
-    ma.af[d] = P->at<const TF>(P->o_mfa[d]);
     ma.hprev[d] = static_cast<const TF*>(in->h_prev[d]);
     ma.rhs[d] = P->at<TF>(P->o_mrhs[d]);
     ma.out[d] = static_cast<TF*>(out->u_tilde[d]);
@@ -940,7 +934,7 @@ int momentum_impl(bcm_plan* P, const bcm_momentum_in* in, bcm_momentum_out* out,
   SolveLog log{rep};
   if (rep) rep->history_len = 0;
   auto launch = [&](int mode) {  // timer class "momentum": the passes over H (explicit step or
-                                 // Crank-Nicolson sweep); "momentum_start": export and CN start
+                                 // Crank-Nicolson sweep); "momentum_start": the CN start
     const int cls = cls_of(mode == MOM_CN_START ? "momentum_start" : "momentum", 0);
     return timed(P, cls, s, [&] { return launch_mom<TF>(NL, mode, ma, grid, s); });
   };
@@ -1332,8 +1326,8 @@ int bcm_plan_create(const bcm_mesh* mesh, const bcm_solver_opts* opts, bcm_plan*
   P->momentum = !M.multilevel && M.n >= 4;
   if (P->momentum) {
     const size_t mfs = size_t(4) * M.n * M.n * nc * Tf;  // two x layers per face (kernels_mom.hip)
+    P->o_mfa = take(top, mfs);
     for (int d = 0; d < 3; ++d) {
-      P->o_mfa[d] = take(top, mfs);
       P->o_mfv[0][d] = take(top, mfs);
       P->o_mfv[1][d] = take(top, mfs);
       P->o_mrhs[d] = take(top, cells * Tf);
