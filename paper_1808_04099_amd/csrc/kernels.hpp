@@ -184,7 +184,6 @@ struct DivArgs {        // b = (rho/dt) div(U*)
   const TF* uf;
   double U_in, inv_c;
   double* b;
-  double* part_bb;
 };
 
 template <typename TF>
@@ -193,7 +192,7 @@ struct CorrectArgs {    // u_new = u* - c G_c p; optional face velocities U* - c
   const double* p;
   const double* pf;
   const TF* ustar[3];
-  const TF* u[3];       // u~, read instead of u* in cubes whose body flag is 0 (16^3 kernel)
+  const TF* u[3];       // u~, read instead of u* in cubes whose body flag is 0 (16^3)
   const uint8_t* body;  // nullptr: u* everywhere
   const TF* uf;
   double U_in, c;
@@ -374,6 +373,8 @@ template <typename T> hipError_t launchc_ir(int NL, const IrArgs<T>& a, hipStrea
 template <typename TF> hipError_t launch16_force(const ForceArgs<TF>& a, hipStream_t s);
 template <typename TF> hipError_t launch16_div(const DivArgs<TF>& a, hipStream_t s);
 template <typename TF> hipError_t launch16_correct(const CorrectArgs<TF>& a, hipStream_t s);
+template <typename TF> hipError_t launch16_adj_gp(const AdjGpArgs<TF>& a, hipStream_t s);
+template <typename TF> hipError_t launch16_adj_rhs(const AdjRhsArgs<TF>& a, hipStream_t s);
 
 // Number of partial sums a column kernel at level NL writes.
 inline int partials_of(int NL, int n_cubes) { return fine_grid(col_units(col_cpb(NL), n_cubes)); }
@@ -382,6 +383,13 @@ inline int partials_of(int NL, int n_cubes) { return fine_grid(col_units(col_cpb
 inline int cubes_per_wg(int NL) {
   const int n3 = NL * NL * NL;
   return n3 >= 256 ? 1 : 256 / n3;
+}
+
+// Workgroups, and partial sums of g_U_in, of the adjoint's last kernel.
+inline int adj_rhs_parts(int NL, int n_cubes) {
+  if (NL == 16) return n_cubes < 2048 ? n_cubes : 2048;
+  const int cpb = cubes_per_wg(NL);
+  return (n_cubes + cpb - 1) / cpb;
 }
 
 }  // namespace bcm

@@ -1373,25 +1373,200 @@ __global__ __launch_bounds__(256) void k16_div(DivArgs<TF> a) {
   }
 }
 
-// u_new = u* - c G_c p (cell velocities only; the face-velocity output uses k_correct).  The
-// x/y neighbours of p go through LDS one plane at a time (two plane buffers used in turn);
-// the halo ring of plane k comes from the lanes with j == k, which hold the x/y face values
-// at z = k (tangential position (t1, t2) = (i, j) of faces 0..3).
-template <typename TF, bool ML>
-__global__ __launch_bounds__(256) void k16_correct(CorrectArgs<TF> a) {
-  __shared__ double pl[2][P16];
+// Transpose of the correction, divided by the cube's volume: out = (g_p + c (G_c G)^T v) / V.
+// A stream of four fields (40 bytes a cell with g_p): v_x and v_y go through LDS one plane at a
+// time (two buffers in turn), v_z stays in registers, and every load is a plane ahead.  8.4M
+// cells took 124 us in the kernel for every cube size, which stages a padded tile per
+// component between two barriers, and 62 us here.
+template <typename TF>
+__global__ __launch_bounds__(256) void k16_adj_gp(AdjGpArgs<TF> a) {
+  __shared__ TF pl[2][2][P16];
   const int t = threadIdx.x, i = t & 15, j = t >> 4;
   const int n = a.g.n_cubes;
   for (int w = blockIdx.x; w < n; w += gridDim.x) {
     const int c = ro_load(a.g.launch, w);
     MetaRO& m = meta_ro(a.g.meta, c);
-    double p[16], hv[6], rf[6];
+    const size_t g0 = (size_t)c * 4096 + t;
+    TF nx = ld_nt(a.v[0] + g0), ny = ld_nt(a.v[1] + g0);  // of the next plane
+    TF z0 = ld_nt(a.v[2] + g0), z1 = ld_nt(a.v[2] + g0 + 256);  // of this plane and the next
+    double ng = a.gp_in ? ld_nt(a.gp_in + g0) : 0.0;
+    TF hv[6];  // v across the faces, as the rule weighs it
+    const auto gf = [&](int q, int of, int aa, int bb) { return face_get(a.vf, q, of, aa, bb); };
+#pragma unroll
+    for (int f = 0; f < 6; ++f) {
+      const int kd = kind_of(m, f);
+      hv[f] = kd <= FK_FINER ? TF(RuleTab<RULE_V>::nbeff(kd)) * nb_raw<16, TF>(m, f, i, j, gf) : TF(0);
+    }
+    const double ch = a.c / m.h, iv = 1.0 / m.vol;  // (vol is a power of two)
+    const double ox_m = i == 0 ? RuleTab<RULE_V>::own(kind_of(m, 0)) : 0.5;
+    const double ox_p = i == 15 ? RuleTab<RULE_V>::own(kind_of(m, 1)) : 0.5;
+    const double oy_m = j == 0 ? RuleTab<RULE_V>::own(kind_of(m, 2)) : 0.5;
+    const double oy_p = j == 15 ? RuleTab<RULE_V>::own(kind_of(m, 3)) : 0.5;
+    const double oz_m = RuleTab<RULE_V>::own(kind_of(m, 4)), oz_p = RuleTab<RULE_V>::own(kind_of(m, 5));
+    const int cc = (j + 1) * 18 + (i + 1);
+    double low = 0.5 * double(hv[4]) + oz_m * double(z0);  // term of the lower z face
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      TF* bx = pl[k & 1][0];
+      TF* by = pl[k & 1][1];
+      const double vx = nx, vy = ny, vz = z0, gp = ng;
+      bx[cc] = nx;
+      by[cc] = ny;
+      if (j == k) {
+        bx[(i + 1) * 18 + 0] = hv[0];   // x = -1, y = i
+        bx[(i + 1) * 18 + 17] = hv[1];  // x = 16, y = i
+        by[0 * 18 + (i + 1)] = hv[2];   // y = -1, x = i
+        by[17 * 18 + (i + 1)] = hv[3];  // y = 16, x = i
+      }
+      TF z2 = TF(0);
+      if (k < 15) {
+        nx = ld_nt(a.v[0] + g0 + (k + 1) * 256);
+        ny = ld_nt(a.v[1] + g0 + (k + 1) * 256);
+        if (k < 14) z2 = ld_nt(a.v[2] + g0 + (k + 2) * 256);
+        ng = a.gp_in ? ld_nt(a.gp_in + g0 + (k + 1) * 256) : 0.0;
+      }
+      __syncthreads();
+      const double up = k < 15 ? 0.5 * (vz + double(z1)) : 0.5 * double(hv[5]) + oz_p * vz;
+      double acc = up - low;
+      acc += (0.5 * double(bx[cc + 1]) + ox_p * vx) - (0.5 * double(bx[cc - 1]) + ox_m * vx);
+      acc += (0.5 * double(by[cc + 18]) + oy_p * vy) - (0.5 * double(by[cc - 18]) + oy_m * vy);
+      st_nt(a.out + g0 + k * 256, (acc * ch + gp) * iv);
+      low = up;
+      z0 = z1;
+      z1 = z2;
+    }
+    __syncthreads();
+  }
+}
+
+// Transpose of the right-hand side and the forcing (see k_adj_rhs): lambda goes through LDS one
+// plane at a time as p does in k16_correct, and the other fields stream past it, one plane
+// ahead.  104 bytes a cell (112 accumulating): 8.4M cells took 310 us with the whole padded
+// tile of lambda in LDS (three workgroups a CU, nothing loaded ahead), and 222 us here.
+template <typename TF, bool ML>
+__global__ __launch_bounds__(256) void k16_adj_rhs(AdjRhsArgs<TF> a) {
+  __shared__ double pl[2][P16];
+  __shared__ double red[8];
+  const int t = threadIdx.x, i = t & 15, j = t >> 4;
+  const int n = a.g.n_cubes;
+  const bool al_on = a.alpha != nullptr, acc_on = al_on && a.galpha && a.accumulate;
+  double gU = 0.0;
+  for (int w = blockIdx.x; w < n; w += gridDim.x) {
+    const int c = ro_load(a.g.launch, w);
+    MetaRO& m = meta_ro(a.g.meta, c);
+    double hv[6], rf[6];
+    Slots S;
+    slots<16, ML>(m, c, i, j, S);
+#pragma unroll
+    for (int f = 0; f < 6; ++f) rf[f] = a.lamf[S.fine[f]];
+    const size_t g0 = (size_t)c * 4096 + t;
+    double z0 = ld_nt(a.lam + g0), z1 = ld_nt(a.lam + g0 + 256);  // of this plane and the next
+#pragma unroll
+    for (int f = 0; f < 6; ++f) hv[f] = S.kind[f] <= FK_FINER ? RuleTab<RULE_L>::nbeff(S.kind[f]) * rf[f] : 0.0;
+    const double ch = a.inv_c / m.h;
+    const double ox_m = i == 0 ? RuleTab<RULE_L>::own(kind_of(m, 0)) : 0.5;
+    const double ox_p = i == 15 ? RuleTab<RULE_L>::own(kind_of(m, 1)) : 0.5;
+    const double oy_m = j == 0 ? RuleTab<RULE_L>::own(kind_of(m, 2)) : 0.5;
+    const double oy_p = j == 15 ? RuleTab<RULE_L>::own(kind_of(m, 3)) : 0.5;
+    const double oz_m = RuleTab<RULE_L>::own(kind_of(m, 4)), oz_p = RuleTab<RULE_L>::own(kind_of(m, 5));
+    // inflow sides of the lane's column (those of its first and last cell apart)
+    const int in_xy = (i == 0 && kind_of(m, 0) == FK_INFLOW) + (i == 15 && kind_of(m, 1) == FK_INFLOW) +
+                      (j == 0 && kind_of(m, 2) == FK_INFLOW) + (j == 15 && kind_of(m, 3) == FK_INFLOW);
+    const int in_lo = kind_of(m, 4) == FK_INFLOW, in_hi = kind_of(m, 5) == FK_INFLOW;
+    const int cc = (j + 1) * 18 + (i + 1);
+    struct Row {
+      TF g[3], u[3], al, ga;
+    } nx;
+    auto fetch = [&](int k) {
+      const size_t g = g0 + k * 256;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        nx.g[d] = ld_nt(a.gun[d] + g);
+        nx.u[d] = al_on ? ld_nt(a.u[d] + g) : TF(0);
+      }
+      nx.al = al_on ? ld_nt(a.alpha + g) : TF(0);
+      nx.ga = acc_on ? ld_nt(a.galpha + g) : TF(0);
+    };
+    fetch(0);
+    double low = oz_m * z0 - 0.5 * hv[4];  // term of the lower z face
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      double* b = pl[k & 1];
+      const double lam = z0;
+      b[cc] = lam;
+      if (j == k) {
+        b[(i + 1) * 18 + 0] = hv[0];   // x = -1, y = i
+        b[(i + 1) * 18 + 17] = hv[1];  // x = 16, y = i
+        b[0 * 18 + (i + 1)] = hv[2];   // y = -1, x = i
+        b[17 * 18 + (i + 1)] = hv[3];  // y = 16, x = i
+      }
+      const Row r = nx;
+      if (k < 15) fetch(k + 1);
+      const double z2 = k < 14 ? ld_nt(a.lam + g0 + (k + 2) * 256) : 0.0;
+      __syncthreads();
+      const double zp = k < 15 ? 0.5 * lam - 0.5 * z1 : oz_p * lam - 0.5 * hv[5];
+      const double zm = low;
+      low = k < 15 ? -zp : 0.0;
+      z0 = z1;
+      z1 = z2;
+      const double df[3] = {(ox_p * lam - 0.5 * b[cc + 1]) - (ox_m * lam - 0.5 * b[cc - 1]),
+                            (oy_p * lam - 0.5 * b[cc + 18]) - (oy_m * lam - 0.5 * b[cc - 18]), zp - zm};
+      const size_t g = g0 + k * 256;
+      const double al = double(r.al);
+      double ga = 0.0;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const double gs = double(r.g[d]) + ch * df[d];
+        if (al_on) {
+          const double us = a.us[d] ? double(a.us[d][g]) : a.usc[d];
+          ga += gs * (us - double(r.u[d]));
+        }
+        st_nt(a.gu[d] + g, TF((1.0 - al) * gs));
+      }
+      if (al_on && a.galpha) st_nt(a.galpha + g, acc_on ? TF(double(r.ga) + ga) : TF(ga));
+      gU -= double(in_xy + (k == 0 ? in_lo : 0) + (k == 15 ? in_hi : 0)) * (ch * lam);
+    }
+    __syncthreads();
+  }
+  if (a.part_gU) {
+    const double tot = block_sum(gU, red);
+    if (t == 0) a.part_gU[blockIdx.x] = tot;
+  }
+}
+
+// u_new = u* - c G_c p and, with FACES, the face velocities U* - c G p.  The x/y neighbours of p
+// (and of u*_x, u*_y) go through LDS one plane at a time (two plane buffers used in turn); the
+// halo ring of plane k comes from the lanes with j == k, which hold the x/y face values at
+// z = k (tangential position (t1, t2) = (i, j) of faces 0..3).  Each lane writes the face on the
+// lower side of its cells, the last cell of a line the upper one as well.  With faces the kernel
+// moves 80 bytes a cell in FP64: 4.2M cells took 324 us with whole padded tiles in LDS, and
+// 93 us here.
+template <typename TF, bool ML, bool FACES>
+__global__ __launch_bounds__(256) void k16_correct(CorrectArgs<TF> a) {
+  __shared__ double pl[2][P16];
+  __shared__ TF vl[FACES ? 2 : 1][FACES ? 2 : 1][FACES ? P16 : 1];  // u*_x and u*_y of a plane
+  const int t = threadIdx.x, i = t & 15, j = t >> 4;
+  const int n = a.g.n_cubes;
+  for (int w = blockIdx.x; w < n; w += gridDim.x) {
+    const int c = ro_load(a.g.launch, w);
+    MetaRO& m = meta_ro(a.g.meta, c);
+    double hv[6], rf[6];
     Slots S;
     slots<16, ML>(m, c, i, j, S);
 #pragma unroll
     for (int f = 0; f < 6; ++f) rf[f] = a.pf[S.fine[f]];
+    TF hu[FACES ? 6 : 1];  // u* across the faces, as the interpolation rule weighs it
+    if constexpr (FACES) {
+      const auto gf = [&](int q, int of, int aa, int bb) { return face_get(a.uf, q, of, aa, bb); };
 #pragma unroll
-    for (int k = 0; k < 16; ++k) p[k] = ld_nt(a.p + (size_t)c * 4096 + k * 256 + t);
+      for (int f = 0; f < 6; ++f) {
+        const int kd = kind_of(m, f);
+        hu[f] = kd <= FK_FINER ? TF(RuleTab<RULE_U>::nbeff(kd)) * nb_raw<16, TF>(m, f, i, j, gf)
+                               : kd == FK_INFLOW ? TF(2.0 * ((f & 1) ? -a.U_in : a.U_in)) : TF(0);
+      }
+    }
+    const size_t g0 = (size_t)c * 4096 + t;
+    double p0 = ld_nt(a.p + g0), p1 = ld_nt(a.p + g0 + 256);  // of this plane and the next
 #pragma unroll
     for (int f = 0; f < 6; ++f) hv[f] = halo_val<double>(S.kind[f], rf[f]);
     const double ch = a.c * 0.5 / m.h;
@@ -1403,40 +1578,83 @@ __global__ __launch_bounds__(256) void k16_correct(CorrectArgs<TF> a) {
     const int cc = (j + 1) * 18 + (i + 1);
     // u* of plane k + 1 is loaded while plane k is computed (the loads would otherwise start
     // only after each plane's barrier)
-    const size_t g0 = (size_t)c * 4096 + t;
     const bool forced = !a.body || ro_byte(a.body, c) != 0;  // u* stored, else u* = u~
     const TF* src[3] = {forced ? a.ustar[0] : a.u[0], forced ? a.ustar[1] : a.u[1],
                         forced ? a.ustar[2] : a.u[2]};
-    TF us[3], usn[3];
+    TF us[3], usn[3], below = FACES ? hu[FACES ? 4 : 0] : TF(0);  // u*_z of the plane below
     // (loaded whether or not the component is written: a load under a branch makes the
     // following waits conservative)
 #pragma unroll
     for (int d = 0; d < 3; ++d) usn[d] = ld_nt(src[d] + g0);
+    double low = hv[4] - oz_m * p0;  // difference across the lower z face
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
       double* b = pl[k & 1];
-      b[cc] = p[k];
+      TF* bx = vl[FACES ? k & 1 : 0][0];
+      TF* by = vl[FACES ? k & 1 : 0][FACES ? 1 : 0];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) us[d] = usn[d];
+      const double p = p0;
+      b[cc] = p;
+      if (FACES) {
+        bx[cc] = us[0];
+        by[cc] = us[1];
+      }
       if (j == k) {
         b[(i + 1) * 18 + 0] = hv[0];   // x = -1, y = i
         b[(i + 1) * 18 + 17] = hv[1];  // x = 16, y = i
         b[0 * 18 + (i + 1)] = hv[2];   // y = -1, x = i
         b[17 * 18 + (i + 1)] = hv[3];  // y = 16, x = i
+        if constexpr (FACES) {
+          bx[(i + 1) * 18 + 0] = hu[0];
+          bx[(i + 1) * 18 + 17] = hu[1];
+          by[0 * 18 + (i + 1)] = hu[2];
+          by[17 * 18 + (i + 1)] = hu[3];
+        }
       }
-#pragma unroll
-      for (int d = 0; d < 3; ++d) us[d] = usn[d];
       if (k < 15) {
 #pragma unroll
         for (int d = 0; d < 3; ++d) usn[d] = ld_nt(src[d] + g0 + (k + 1) * 256);
       }
+      const double p2 = k < 14 ? ld_nt(a.p + g0 + (k + 2) * 256) : 0.0;
       __syncthreads();
       const size_t g = g0 + k * 256;
-      const double gx = (b[cc + 1] - ox_p * p[k]) - (b[cc - 1] - ox_m * p[k]);
-      const double gy = (b[cc + 18] - oy_p * p[k]) - (b[cc - 18] - oy_m * p[k]);
-      const double zp = k < 15 ? p[k < 15 ? k + 1 : 15] - p[k] : hv[5] - oz_p * p[k];
-      const double zm = k > 0 ? p[k > 0 ? k - 1 : 0] - p[k] : hv[4] - oz_m * p[k];
-      if (a.unew[0]) st_nt(a.unew[0] + g, TF(double(us[0]) - ch * gx));
-      if (a.unew[1]) st_nt(a.unew[1] + g, TF(double(us[1]) - ch * gy));
+      // undivided outward differences of p on the six sides
+      const double xp = b[cc + 1] - ox_p * p, xm = b[cc - 1] - ox_m * p;
+      const double yp = b[cc + 18] - oy_p * p, ym = b[cc - 18] - oy_m * p;
+      const double zp = k < 15 ? p1 - p : hv[5] - oz_p * p;
+      const double zm = low;
+      low = -zp;
+      p0 = p1;
+      p1 = p2;
+      if (a.unew[0]) st_nt(a.unew[0] + g, TF(double(us[0]) - ch * (xp - xm)));
+      if (a.unew[1]) st_nt(a.unew[1] + g, TF(double(us[1]) - ch * (yp - ym)));
       if (a.unew[2]) st_nt(a.unew[2] + g, TF(double(us[2]) - ch * (zp - zm)));
+      if constexpr (FACES) {
+        // U* - c dp/dn; d: undivided outward difference of p, sg: the outward sign
+        const double cf = 2.0 * ch;
+        auto face = [&](double nb, double own, double u, double d, double sg) {
+          return TF(0.5 * nb + own * u - sg * cf * d);
+        };
+        auto own = [&](bool edge, int f) { return edge ? RuleTab<RULE_U>::own(kind_of(m, f)) : 0.5; };
+        const size_t fc = (size_t)c * 17 * 256;
+        if (a.face_u[0]) {
+          TF* o = a.face_u[0] + fc + (k * 16 + j) * 17;
+          st_nt(o + i, face(double(bx[cc - 1]), own(i == 0, 0), double(us[0]), xm, -1.0));
+          if (i == 15) st_nt(o + 16, face(double(bx[cc + 1]), own(true, 1), double(us[0]), xp, 1.0));
+        }
+        if (a.face_u[1]) {
+          TF* o = a.face_u[1] + fc + k * 17 * 16 + i;
+          st_nt(o + j * 16, face(double(by[cc - 18]), own(j == 0, 2), double(us[1]), ym, -1.0));
+          if (j == 15) st_nt(o + 16 * 16, face(double(by[cc + 18]), own(true, 3), double(us[1]), yp, 1.0));
+        }
+        if (a.face_u[2]) {
+          TF* o = a.face_u[2] + fc + t;
+          st_nt(o + k * 256, face(double(below), own(k == 0, 4), double(us[2]), zm, -1.0));
+          if (k == 15) st_nt(o + 16 * 256, face(double(hu[5]), own(true, 5), double(us[2]), zp, 1.0));
+        }
+        below = us[2];
+      }
     }
     __syncthreads();
   }
@@ -1542,10 +1760,24 @@ hipError_t launch16_div(const DivArgs<TF>& a, hipStream_t s) {
 }
 template <typename TF>
 hipError_t launch16_correct(const CorrectArgs<TF>& a, hipStream_t s) {
-  if (a.g.multilevel)
-    hipLaunchKernelGGL((k16_correct<TF, true>), dim3(std::min(a.g.n_cubes, 2048)), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL((k16_correct<TF, false>), dim3(std::min(a.g.n_cubes, 2048)), dim3(256), 0, s, a);
+  const dim3 grid(std::min(a.g.n_cubes, 2048)), block(256);
+  const bool faces = a.face_u[0] || a.face_u[1] || a.face_u[2];
+  if (a.g.multilevel && faces) hipLaunchKernelGGL((k16_correct<TF, true, true>), grid, block, 0, s, a);
+  else if (a.g.multilevel) hipLaunchKernelGGL((k16_correct<TF, true, false>), grid, block, 0, s, a);
+  else if (faces) hipLaunchKernelGGL((k16_correct<TF, false, true>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((k16_correct<TF, false, false>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+template <typename TF>
+hipError_t launch16_adj_gp(const AdjGpArgs<TF>& a, hipStream_t s) {
+  hipLaunchKernelGGL((k16_adj_gp<TF>), dim3(std::min(a.g.n_cubes, 2048)), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+template <typename TF>
+hipError_t launch16_adj_rhs(const AdjRhsArgs<TF>& a, hipStream_t s) {
+  const dim3 grid(adj_rhs_parts(16, a.g.n_cubes)), block(256);
+  if (a.g.multilevel) hipLaunchKernelGGL((k16_adj_rhs<TF, true>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((k16_adj_rhs<TF, false>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 
@@ -1557,7 +1789,9 @@ hipError_t launch16_correct(const CorrectArgs<TF>& a, hipStream_t s) {
   template hipError_t launchc_ir<T>(int, const IrArgs<T>&, hipStream_t);              \
   template hipError_t launch16_force<T>(const ForceArgs<T>&, hipStream_t);            \
   template hipError_t launch16_div<T>(const DivArgs<T>&, hipStream_t);                \
-  template hipError_t launch16_correct<T>(const CorrectArgs<T>&, hipStream_t);
+  template hipError_t launch16_correct<T>(const CorrectArgs<T>&, hipStream_t);        \
+  template hipError_t launch16_adj_gp<T>(const AdjGpArgs<T>&, hipStream_t);           \
+  template hipError_t launch16_adj_rhs<T>(const AdjRhsArgs<T>&, hipStream_t);
 BCM_INSTC(float)
 BCM_INSTC(double)
 

@@ -83,7 +83,6 @@ __global__ __launch_bounds__(256) void k_div(DivArgs<TF> a) {
   __shared__ CubeMeta sm[L::CPB];
   __shared__ int cube[L::CPB];
   __shared__ TF tile[L::CPB * L::TILE];
-  __shared__ double red[8];
   load_meta<NL>(sm, cube, a.g.meta, a.g.launch, a.g.n_cubes);
   double acc[R];
 #pragma unroll
@@ -117,7 +116,6 @@ __global__ __launch_bounds__(256) void k_div(DivArgs<TF> a) {
     }
     __syncthreads();
   }
-  double bb = 0.0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int e = threadIdx.x + r * WG;
@@ -126,13 +124,7 @@ __global__ __launch_bounds__(256) void k_div(DivArgs<TF> a) {
     cell_of<NL>(e, s, i, j, k);
     const int c = cube[s];
     if (c < 0) continue;
-    const double b = acc[r] * a.inv_c;
-    a.b[(size_t)c * L::N3 + (e - s * L::N3)] = b;
-    bb += sm[s].vol * b * b;
-  }
-  if (a.part_bb) {
-    const double t = block_sum(bb, red);
-    if (threadIdx.x == 0) a.part_bb[blockIdx.x] = t;
+    a.b[(size_t)c * L::N3 + (e - s * L::N3)] = acc[r] * a.inv_c;
   }
 }
 
@@ -352,9 +344,9 @@ __global__ __launch_bounds__(256) void k_kinetic(KineticArgs<TF> a) {
 
 }  // namespace
 
+// (16^3 cubes have kernels of their own in kernels_col.hip)
 #define BCM_DISPATCH_NL(NLV, CALL)                    \
   switch (NLV) {                                      \
-    case 16: { constexpr int NLC = 16; CALL; } break; \
     case 8: { constexpr int NLC = 8; CALL; } break;   \
     case 4: { constexpr int NLC = 4; CALL; } break;   \
     case 2: { constexpr int NLC = 2; CALL; } break;   \
@@ -374,23 +366,25 @@ hipError_t launch_force(int NL, const ForceArgs<TF>& a, hipStream_t s) {
 }
 template <typename TF>
 hipError_t launch_div(int NL, const DivArgs<TF>& a, hipStream_t s) {
-  if (NL == 16 && !a.part_bb) return launch16_div<TF>(a, s);
+  if (NL == 16) return launch16_div<TF>(a, s);
   BCM_DISPATCH_NL(NL, hipLaunchKernelGGL((k_div<NLC, TF>), dim3(n_wg(NLC, a.g.n_cubes)), dim3(WG), 0, s, a));
   return hipGetLastError();
 }
 template <typename TF>
 hipError_t launch_correct(int NL, const CorrectArgs<TF>& a, hipStream_t s) {
-  if (NL == 16 && !a.face_u[0] && !a.face_u[1] && !a.face_u[2]) return launch16_correct<TF>(a, s);
+  if (NL == 16) return launch16_correct<TF>(a, s);
   BCM_DISPATCH_NL(NL, hipLaunchKernelGGL((k_correct<NLC, TF>), dim3(n_wg(NLC, a.g.n_cubes)), dim3(WG), 0, s, a));
   return hipGetLastError();
 }
 template <typename TF>
 hipError_t launch_adj_gp(int NL, const AdjGpArgs<TF>& a, hipStream_t s) {
+  if (NL == 16) return launch16_adj_gp<TF>(a, s);
   BCM_DISPATCH_NL(NL, hipLaunchKernelGGL((k_adj_gp<NLC, TF>), dim3(n_wg(NLC, a.g.n_cubes)), dim3(WG), 0, s, a));
   return hipGetLastError();
 }
 template <typename TF>
 hipError_t launch_adj_rhs(int NL, const AdjRhsArgs<TF>& a, hipStream_t s) {
+  if (NL == 16) return launch16_adj_rhs<TF>(a, s);
   BCM_DISPATCH_NL(NL, hipLaunchKernelGGL((k_adj_rhs<NLC, TF>), dim3(n_wg(NLC, a.g.n_cubes)), dim3(WG), 0, s, a));
   return hipGetLastError();
 }

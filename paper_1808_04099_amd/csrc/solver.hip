@@ -214,11 +214,6 @@ int finalize(bcm_plan* P, int op, int which0, int which1, int nparts, int first,
   return BCM_OK;
 }
 
-int n_wg(int NL, int nc) {
-  const int c = cubes_per_wg(NL);
-  return (nc + c - 1) / c;
-}
-
 // Export the faces of an FP64 field (kc_ir without an update).
 int export64(bcm_plan* P, double* x, double* xf, hipStream_t s) {
   IrArgs<float> a{geom(P, P->n), x, nullptr, xf, 0.0};
@@ -766,9 +761,8 @@ int project_impl(bcm_plan* P, const bcm_project_in* in, bcm_project_out* out, bc
   }
   fa.uf = P->at<TF>(P->o_uf);
   // 16^3 kernels: force and store u* only in cubes that hold some alpha != 0; the others pass
-  // u~ on (the face-velocity output needs the generic correction, which reads u* everywhere)
-  const bool sel = NL == 16 && !out->face_u[0] && !out->face_u[1] && !out->face_u[2];
-  fa.body = sel ? P->at<uint8_t>(P->o_body) : nullptr;
+  // u~ on
+  fa.body = NL == 16 ? P->at<uint8_t>(P->o_body) : nullptr;
   HIPCHK(timed(P, cls_of("force", 0), s, [&] { return launch_force<TF>(NL, fa, s); }), "k_force");
   double* p = out->p;
   int st = BCM_OK;
@@ -827,15 +821,26 @@ int adjoint_impl(bcm_plan* P, const bcm_adjoint_in* in, bcm_adjoint_out* out, bc
   const int NL = P->n;
   const double c = in->dt / in->rho;
   TF* vf = P->at<TF>(P->o_uf);
-  ExportArgs<TF, TF> ea{};
-  ea.g = geom(P, NL);
-  ea.xf = vf;
-  ea.comp_faces = 1;
-  for (int d = 0; d < 3; ++d) ea.x3[d] = static_cast<const TF*>(in->g_u_new[d]);
-  HIPCHK(timed(P, cls_of("export", 0), s, [&] { return launch_export<TF, TF>(NL, ea, s); }), "export g_u faces");
+  const TF* gun[3];
+  for (int d = 0; d < 3; ++d) gun[d] = static_cast<const TF*>(in->g_u_new[d]);
+  if (NL == 16) {  // the forcing kernel without a body writes the face-normal slabs only
+    ForceArgs<TF> ea{};
+    ea.g = geom(P, NL);
+    for (int d = 0; d < 3; ++d) ea.u[d] = gun[d];
+    ea.uf = vf;
+    ea.body = P->at<uint8_t>(P->o_body);
+    HIPCHK(timed(P, cls_of("export", 0), s, [&] { return launch_force<TF>(NL, ea, s); }), "export g_u faces");
+  } else {
+    ExportArgs<TF, TF> ea{};
+    ea.g = geom(P, NL);
+    ea.xf = vf;
+    ea.comp_faces = 1;
+    for (int d = 0; d < 3; ++d) ea.x3[d] = gun[d];
+    HIPCHK(timed(P, cls_of("export", 0), s, [&] { return launch_export<TF, TF>(NL, ea, s); }), "export g_u faces");
+  }
   AdjGpArgs<TF> ga{};
   ga.g = geom(P, NL);
-  for (int d = 0; d < 3; ++d) ga.v[d] = ea.x3[d];
+  for (int d = 0; d < 3; ++d) ga.v[d] = gun[d];
   ga.vf = vf;
   ga.gp_in = in->g_p;
   ga.c = c;
@@ -847,16 +852,15 @@ int adjoint_impl(bcm_plan* P, const bcm_adjoint_in* in, bcm_adjoint_out* out, bc
   if (P->M->multilevel) {
     ScaleArgs sa{P->at<const CubeMeta>(P->o_meta), P->nc, NL * NL * NL, lam, lam, +1};
     HIPCHK(launch_scale(sa, s), "k_scale");
-  }
-  int e = export64(P, lam, P->at<double>(P->o_pf), s);
-  if (e) return e;
+    if (const int e = export64(P, lam, P->at<double>(P->o_pf), s)) return e;
+  }  // (else the solve left the faces of lam exported)
   AdjRhsArgs<TF> ra{};
   ra.g = geom(P, NL);
   ra.lam = lam;
   ra.lamf = P->at<const double>(P->o_pf);
   ra.alpha = static_cast<const TF*>(in->alpha);
   for (int d = 0; d < 3; ++d) {
-    ra.gun[d] = ea.x3[d];
+    ra.gun[d] = gun[d];
     ra.u[d] = static_cast<const TF*>(in->u[d]);
     ra.us[d] = static_cast<const TF*>(in->us[d]);
     ra.usc[d] = in->us_const[d];
@@ -867,9 +871,9 @@ int adjoint_impl(bcm_plan* P, const bcm_adjoint_in* in, bcm_adjoint_out* out, bc
   ra.inv_c = 1.0 / c;
   ra.part_gU = P->at<double>(P->o_part[0]);
   HIPCHK(timed(P, cls_of("adj_rhs", 0), s, [&] { return launch_adj_rhs<TF>(NL, ra, s); }), "k_adj_rhs");
-  if ((e = finalize(P, OP_GU, 0, -1, n_wg(NL, P->nc), 0, s))) return e;
+  if (const int e = finalize(P, OP_GU, 0, -1, adj_rhs_parts(NL, P->nc), 0, s)) return e;
   Scalars hs{};
-  if ((e = read_scalars(P, &hs, s))) return e;
+  if (const int e = read_scalars(P, &hs, s)) return e;
   out->g_U_in = (out->accumulate ? out->g_U_in : 0.0) + hs.gU;
   if (out->lambda)
     HIPCHK(hipMemcpyAsync(out->lambda, lam, P->cells * sizeof(double), hipMemcpyDeviceToDevice, s), "copy lambda");
