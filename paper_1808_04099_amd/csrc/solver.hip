@@ -403,9 +403,11 @@ constexpr double kStallFactor = 0.99;  // progress = the residual norm falls bel
 // defer: on a normal return the last pending x update is not launched but handed to the
 // caller in *defer (defer->p != nullptr), which must apply it (the mixed path folds it into
 // the refinement update).
+// carry: the first direction is made A-orthogonal to the last one of the previous solve on this
+// plan (flexible CG; the two residuals may be scaled differently, beta absorbs the factor).
 template <typename T>
 int krylov(bcm_plan* P, T* x, bool x_zero, double thr, int max_iter, double hist_scale, SolveLog& log,
-           Scalars* hs, hipStream_t s, UpdateArgs<T>* defer = nullptr) {
+           Scalars* hs, hipStream_t s, UpdateArgs<T>* defer = nullptr, bool carry = false) {
   const int NL = P->n;
   const int nparts = partials_of(NL, P->nc);
   T* r = P->at<T>(P->o_r);
@@ -528,7 +530,8 @@ int krylov(bcm_plan* P, T* x, bool x_zero, double thr, int max_iter, double hist
         break;
       }
     }
-    int st = vcycle<T>(P, (flex && it > 0) ? q : nullptr, s,
+    const bool first = !fcg || (it == 0 && !(flex && carry));  // no direction to orthogonalise against
+    int st = vcycle<T>(P, (flex && !first) ? q : nullptr, s,
                        [&](CoarseMGArgs<T>* carrier) { return start_x(true, carrier); },
                        r_pending ? &ur : nullptr,
                        [&](bool& stop_) -> int {
@@ -543,11 +546,11 @@ int krylov(bcm_plan* P, T* x, bool x_zero, double thr, int max_iter, double hist
                        stop);
     if (st) return finish(st);
     if (stop) break;
-    if ((st = finalize(P, OP_ZRZQ, 0, (flex && it > 0) ? 1 : -1, nparts, !fcg || it == 0, s))) return finish(st);
+    if ((st = finalize(P, OP_ZRZQ, 0, (flex && !first) ? 1 : -1, nparts, first, s))) return finish(st);
     if ((st = join_x())) return finish(st);
     ApplyArgs<T> aa{geom(P, NL), z, P->at<T>(P->o_zf[1]), p, P->at<T>(P->o_pfk[P->pf_cur]),
                     P->at<T>(P->o_pfk[P->pf_cur ^ 1]), q, P->at<const Scalars>(P->o_sc),
-                    (!fcg || it == 0) ? 1 : 0, P->at<double>(P->o_part[2])};
+                    first ? 1 : 0, P->at<double>(P->o_part[2])};
     HIPCHK(timed(P, cls_of("apply", NL), s, [&] { return launch_apply<T>(NL, aa, s); }), "kc_apply");
     P->pf_cur ^= 1;
     if ((st = finalize(P, OP_PQ, 2, -1, nparts, 0, s))) return finish(st);
@@ -583,6 +586,13 @@ int residual64(bcm_plan* P, const double* p, const double* b, TO* r, double rsca
   HIPCHK(timed(P, cls_of("resid64", 0), s, [&] { return launch_resid64<TO>(NL, ra, s); }), "kc_resid64");
   return finalize(P, OP_BB, 0, 1, partials_of(NL, P->nc), 0, s);
 }
+
+// The last search direction is carried into the next refinement step while the true <r, r> is at
+// most this many times the recurrence's: the new residual is then the old one but for a little
+// rounding, and still orthogonal to that direction.  Where FP32 rounding made most of the new
+// residual (ten times the recurrence's norm on a rough right-hand side), carrying the direction
+// slowed that solve from 13 to 23 iterations.
+constexpr double kCarryMax = 1.2;
 
 constexpr double kFp64Floor = 64 * 2.220446049250313e-16;  // relative residual FP64 can reach
 
@@ -664,6 +674,7 @@ int poisson(bcm_plan* P, const double* b, double* p, bool use_guess, bcm_report*
     // inner solve is scaled to unit RMS (by the predicted norm) so FP32 range never matters.
     const double vol = double(P->cells);
     double rscale = 1.0, rr_prev = HUGE_VAL;
+    double rr_before = 0.0, rr_est = 0.0;  // <r, r> before the last inner solve, its estimate after
     int slow = 0;  // consecutive refinement steps that did not halve the residual norm
     for (outer = 0; outer < o.max_outer; ++outer) {
       float* r32 = P->at<float>(P->o_r);
@@ -700,14 +711,20 @@ int poisson(bcm_plan* P, const double* b, double* p, bool use_guess, bcm_report*
         if ((st = residual64<float>(P, pg, b, r32, rscale, s, faces_ok))) return fail(st);
       }
       float* d = P->at<float>(P->o_d);
-      // reduce the residual by inner_tol, or only by what is still missing to reach tol
-      // (with a factor 0.3 of margin), whichever is the weaker requirement
-      const double need = 0.3 * o.tol * std::sqrt(bb / rr);
-      const double red_target = std::max(o.inner_tol, std::min(need, 0.1));
+      // Reduce the residual by inner_tol, or only by what is still missing to reach tol (with a
+      // factor 0.3 of margin), whichever is the weaker requirement.  But when one inner solve
+      // can reach tol by going further than inner_tol, and that lies well above what FP32
+      // rounding left of the previous one, let it (factor 0.5 of margin, as in FP64 mode): a
+      // further refinement step costs two passes in FP64 for one or two iterations.
+      const double miss = o.tol * std::sqrt(bb / rr);
+      const double rounding = outer > 0 ? std::sqrt(std::max(rr - rr_est, 0.0) / rr_before) : 1.0;
+      const bool reach = 0.5 * miss >= 0.01 * o.inner_tol && 0.5 * miss >= 4.0 * rounding;
+      const double red_target = reach ? std::min(0.5 * miss, 0.1) : std::max(o.inner_tol, std::min(0.3 * miss, 0.1));
+      rr_before = rr;
       const double thr = red_target * red_target * rr * rscale * rscale;
       UpdateArgs<float> last{};  // the inner solve's last x update, folded into kc_ir
       if ((st = krylov<float>(P, d, true, thr, o.max_iter, 1.0 / (rscale * std::sqrt(bb)), log, &hs, s,
-                              &last)))
+                              &last, outer > 0 && rr <= kCarryMax * rr_est)))
         return fail(st);
       IrArgs<float> ia{geom(P, P->n), p, d, P->at<double>(P->o_pf), 1.0 / rscale, p_unwritten ? 1 : 0,
                        last.p, last.sc, last.p ? last.x_zero : 0};
@@ -715,7 +732,7 @@ int poisson(bcm_plan* P, const double* b, double* p, bool use_guess, bcm_report*
       p_unwritten = false;
       faces_ok = true;  // kc_ir exports the faces of the updated p
       unchecked = true;
-      const double rr_est = hs.rr / (rscale * rscale);
+      rr_est = hs.rr / (rscale * rscale);
       if (rr_est > 0 && std::isfinite(rr_est)) rscale = 1.0 / std::sqrt(rr_est / vol);
     }
     if (p_unwritten) {  // converged without a refinement step (a tolerance of 1 or more)
