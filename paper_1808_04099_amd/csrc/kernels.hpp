@@ -62,8 +62,13 @@ struct SmoothArgs {
   // is loaded and stored back, with the partial sums of <r, r>_V (one per workgroup, zeros
   // up to fine_grid(units)); upd_q == nullptr: b is used as it is
   const T* upd_q;
-  const Scalars* upd_sc;
+  Scalars* upd_sc;
   double* part_rr;
+  // <p, q> as the apply's partial sums, from which every workgroup forms alpha = <z, r> / <p, q>
+  // and the first one stores both; nullptr: alpha is taken from upd_sc
+  const double* part_pq;
+  int n_pq;
+  int* n_wg;            // host: receives the number of workgroups launched (nullptr: not wanted)
 };
 
 template <typename T>
@@ -82,9 +87,16 @@ struct ApplyArgs {      // p = z + beta p (p = z on the first step); q = A p; <p
   const T* pf_in;
   T* pf_out;
   T* q;
-  const Scalars* sc;
+  Scalars* sc;
   int first;
   double* part;
+  // <z, r> and <z, q_old> as the post-smoother's partial sums, from which every workgroup forms
+  // flexible CG's beta = -<z, q_old> / <p_old, q_old> and the first one stores all three;
+  // nullptr: beta is taken from sc
+  const double* part_zr;
+  const double* part_zq;
+  int n_zr;
+  int* n_wg;            // host: receives the number of workgroups launched (nullptr: not wanted)
 };
 
 template <typename T>

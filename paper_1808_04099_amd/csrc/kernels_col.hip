@@ -269,6 +269,38 @@ __device__ __forceinline__ T nbsum_z(const T* tile, const int (&zb)[4], int o, c
   return tile[zb[0] + o] + tile[zb[1] + o] + tile[zb[2] + o] + tile[zb[3] + o] + zm + zp;
 }
 
+// The partial sums of a previous launch, summed by every workgroup in one fixed order (lane t
+// takes entries t, t + 256, ..., then the wavefronts in order): the launch that needs a
+// recurrence's scalar reduces it itself.  A finalize launch in between costs about 6 us (4.6 us
+// and the gap), this about 1 us at the start of the kernel, while its first loads are in
+// flight: 64 cubes of 16^3 in FP64 1285 -> 1233 us a projection.
+struct Parts {
+  double s0 = 0.0, s1 = 0.0;
+  __device__ void load(const double* p0, const double* p1, int n) {
+#pragma unroll 4
+    for (int e = threadIdx.x; e < n; e += 256) {
+      s0 += p0[e];
+      if (p1) s1 += p1[e];
+    }
+  }
+  // sums on every lane; sh: 8 doubles
+  __device__ void reduce(double* sh) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      s0 += __shfl_down(s0, o, 64);
+      s1 += __shfl_down(s1, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+      sh[threadIdx.x >> 6] = s0;
+      sh[4 + (threadIdx.x >> 6)] = s1;
+    }
+    __syncthreads();
+    s0 = ((sh[0] + sh[1]) + sh[2]) + sh[3];
+    s1 = ((sh[4] + sh[5]) + sh[6]) + sh[7];
+    __syncthreads();
+  }
+};
+
 // Zero the partial sums past the grid, up to the count the reduction reads.
 __device__ __forceinline__ void zero_tail(double* part, int units) {
   for (int k = blockIdx.x + gridDim.x; k < fine_grid(units); k += gridDim.x) part[k] = 0.0;
@@ -541,7 +573,11 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? (NL == 8 ? 4 : 3) : 2) void k
   const bool rfx = RFX && a.rfx != nullptr;
   // pre-smoother of level 0: the r update of the previous Krylov step, fused in
   constexpr bool upd = !POST && UPD;
-  const T ual = upd ? T(a.upd_sc->alpha) : T(0);
+  T ual = T(0);
+  Parts sums;
+  if constexpr (upd) {
+    if (a.part_pq) sums.load(a.part_pq, nullptr, a.n_pq);
+  }
   T nq[upd ? NL : 1];
   auto fetch = [&](int cc) {
 #pragma unroll
@@ -605,6 +641,20 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? (NL == 8 ? 4 : 3) : 2) void k
     if (u + G < U) coarse_ent<NL>(a.nb27, a.g.n_cubes, u + G, entn);
   }
   if (PF && u < U) fetch(c < 0 ? 0 : c);
+  if constexpr (upd) {
+    if (a.part_pq) {  // alpha as k_finalize forms it
+      const double zr_now = a.upd_sc->zr;
+      sums.reduce(red);
+      const double al = sums.s0 != 0.0 ? zr_now / sums.s0 : 0.0;
+      ual = T(al);
+      if (blockIdx.x == 0 && t == 0) {
+        a.upd_sc->pq = sums.s0;
+        a.upd_sc->alpha = al;
+      }
+    } else {
+      ual = T(a.upd_sc->alpha);
+    }
+  }
   double zr = 0.0, zq = 0.0, rrs = 0.0;
   while (u < U) {
     const int ce = c < 0 ? 0 : c;
@@ -990,7 +1040,10 @@ __global__ __launch_bounds__(256) void kc_apply(ApplyArgs<T> a) {
   const LaneC<NL> L(t);
   const int i = L.i, j = L.j;
   const int U = col_units(C::CPB, a.g.n_cubes), G = gridDim.x;
-  const T beta = a.first ? T(0) : T(a.sc->beta);
+  T beta = T(0);
+  const bool lazy = a.part_zr != nullptr;
+  Parts sums;
+  if (lazy && (!a.first || blockIdx.x == 0)) sums.load(a.part_zr, a.first ? nullptr : a.part_zq, a.n_zr);
   T nz[NL], np[NL], rz[6], rp[6];
   int kinds[6];
   auto fetch = [&](int cc) {
@@ -1020,6 +1073,19 @@ __global__ __launch_bounds__(256) void kc_apply(ApplyArgs<T> a) {
   int u = blockIdx.x;
   int c = u < U ? unit_cube<NL>(a.g, u, L.s) : -1;
   if (PF && u < U) fetch(c < 0 ? 0 : c);
+  if (lazy && (!a.first || blockIdx.x == 0)) {  // the recurrence as k_finalize forms it
+    const double pq_old = a.sc->pq;
+    sums.reduce(red);
+    const double be = a.first || pq_old == 0.0 ? 0.0 : -sums.s1 / pq_old;
+    beta = T(be);
+    if (blockIdx.x == 0 && t == 0) {
+      a.sc->zr = sums.s0;
+      a.sc->zq = sums.s1;
+      a.sc->beta = be;
+    }
+  } else if (!a.first) {
+    beta = T(a.sc->beta);
+  }
   double pq = 0.0;
   while (u < U) {
     const int ce = c < 0 ? 0 : c;
@@ -1664,35 +1730,33 @@ __global__ __launch_bounds__(256) void k16_correct(CorrectArgs<TF> a) {
 
 // Persistent grid of one kernel: every workgroup resident at once (CUs x occupancy), rounded
 // down to a multiple of 8 so each workgroup keeps to one XCD's stretch of the launch table.
-static int grid_for(const void* fn, int units) {
-  static int cus = 0;
-  if (!cus) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      cus = 256;
-  }
-  int per = 0;
+static int resident(const void* fn) {
+  int dev = 0, cus = 0, per = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+    cus = 256;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, 256, 0) != hipSuccess || per < 1) per = 1;
-  int g = cus * per;
-  if (g >= 8) g -= g % 8;
-  return std::max(1, std::min(g, fine_grid(units)));
+  const int g = cus * per;
+  return g >= 8 ? g - g % 8 : g;
 }
 
-template <class K, class A>
-static hipError_t launch_col(K kernel, int cpb, const A& a, hipStream_t s) {
+// (the resident count is asked for once per kernel: the query costs about as much as a launch)
+template <auto kernel, class A>
+static hipError_t launch_col(int cpb, const A& a, hipStream_t s, int* n_wg = nullptr) {
+  static const int most = resident(reinterpret_cast<const void*>(kernel));
   const int units = col_units(cpb, a.g.n_cubes);
-  hipLaunchKernelGGL(kernel, dim3(grid_for(reinterpret_cast<const void*>(kernel), units)), dim3(256),
-                     0, s, a);
+  const int grid = std::max(1, std::min(most, fine_grid(units)));
+  if (n_wg) *n_wg = grid;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
-#define BCM_COL_NL(NL, CALL)                            \
-  switch (NL) {                                         \
-    case 16: { constexpr int NLC = 16; CALL; } break;   \
-    case 8: { constexpr int NLC = 8; CALL; } break;     \
-    case 4: { constexpr int NLC = 4; CALL; } break;     \
-    case 2: { constexpr int NLC = 2; CALL; } break;     \
+#define BCM_COL_NL(NL, ...)                                  \
+  switch (NL) {                                              \
+    case 16: { constexpr int NLC = 16; __VA_ARGS__; } break; \
+    case 8: { constexpr int NLC = 8; __VA_ARGS__; } break;   \
+    case 4: { constexpr int NLC = 4; __VA_ARGS__; } break;   \
+    case 2: { constexpr int NLC = 2; __VA_ARGS__; } break;   \
     default: return hipErrorInvalidValue;               \
   }
 
@@ -1701,38 +1765,38 @@ hipError_t launchc_smooth(int NL, const SmoothArgs<T>& a, hipStream_t s) {
   BCM_COL_NL(NL, {
     constexpr int cpb = Col<NLC>::CPB;
     if (a.g.multilevel) {
-      if (a.zero_init && a.upd_q) return launch_col(kc_smooth<T, NLC, false, true, false, true>, cpb, a, s);
-      if (a.zero_init) return launch_col(kc_smooth<T, NLC, false, true>, cpb, a, s);
-      return launch_col(kc_smooth<T, NLC, true, true>, cpb, a, s);
+      if (a.zero_init && a.upd_q) return launch_col<kc_smooth<T, NLC, false, true, false, true>>(cpb, a, s, a.n_wg);
+      if (a.zero_init) return launch_col<kc_smooth<T, NLC, false, true>>(cpb, a, s, a.n_wg);
+      return launch_col<kc_smooth<T, NLC, true, true>>(cpb, a, s, a.n_wg);
     }
-    if (a.zero_init && a.upd_q) return launch_col(kc_smooth<T, NLC, false, false, false, true>, cpb, a, s);
-    if (a.zero_init) return launch_col(kc_smooth<T, NLC, false, false>, cpb, a, s);
-    if (a.nb27) return launch_col(kc_smooth<T, NLC, true, false, true>, cpb, a, s);
-    return launch_col(kc_smooth<T, NLC, true, false>, cpb, a, s);
+    if (a.zero_init && a.upd_q) return launch_col<kc_smooth<T, NLC, false, false, false, true>>(cpb, a, s, a.n_wg);
+    if (a.zero_init) return launch_col<kc_smooth<T, NLC, false, false>>(cpb, a, s, a.n_wg);
+    if (a.nb27) return launch_col<kc_smooth<T, NLC, true, false, true>>(cpb, a, s, a.n_wg);
+    return launch_col<kc_smooth<T, NLC, true, false>>(cpb, a, s, a.n_wg);
   });
   return hipSuccess;
 }
 template <typename T>
 hipError_t launchc_rfix(int NL, const RestrictFixArgs<T>& a, hipStream_t s) {
   BCM_COL_NL(NL, {
-    if (a.g.multilevel) return launch_col(kc_rfix<T, NLC, true>, Col<NLC>::CPB, a, s);
-    return launch_col(kc_rfix<T, NLC, false>, Col<NLC>::CPB, a, s);
+    if (a.g.multilevel) return launch_col<kc_rfix<T, NLC, true>>(Col<NLC>::CPB, a, s);
+    return launch_col<kc_rfix<T, NLC, false>>(Col<NLC>::CPB, a, s);
   });
   return hipSuccess;
 }
 template <typename T>
 hipError_t launchc_apply(int NL, const ApplyArgs<T>& a, hipStream_t s) {
   BCM_COL_NL(NL, {
-    if (a.g.multilevel) return launch_col(kc_apply<T, NLC, true>, Col<NLC>::CPB, a, s);
-    return launch_col(kc_apply<T, NLC, false>, Col<NLC>::CPB, a, s);
+    if (a.g.multilevel) return launch_col<kc_apply<T, NLC, true>>(Col<NLC>::CPB, a, s, a.n_wg);
+    return launch_col<kc_apply<T, NLC, false>>(Col<NLC>::CPB, a, s, a.n_wg);
   });
   return hipSuccess;
 }
 template <typename TO>
 hipError_t launchc_resid64(int NL, const Resid64Args<TO>& a, hipStream_t s) {
   BCM_COL_NL(NL, {
-    if (a.g.multilevel) return launch_col(kc_resid64<TO, NLC, true>, Col<NLC>::CPB, a, s);
-    return launch_col(kc_resid64<TO, NLC, false>, Col<NLC>::CPB, a, s);
+    if (a.g.multilevel) return launch_col<kc_resid64<TO, NLC, true>>(Col<NLC>::CPB, a, s);
+    return launch_col<kc_resid64<TO, NLC, false>>(Col<NLC>::CPB, a, s);
   });
   return hipSuccess;
 }

@@ -164,7 +164,10 @@ hipError_t timed(bcm_plan* P, int cls, hipStream_t s, F&& launch) {
   return err;
 }
 
-int cls_of(const char* base, int NL) {
+// Index of a timer class (with the level's edge length appended, or as it stands); only asked for
+// while a class is timed.
+int cls_of(const bcm_plan* P, const char* base, int NL) {
+  if (P->timer.cls < 0) return -2;
   char name[32];
   std::snprintf(name, sizeof(name), "%s%d", base, NL);
   for (int i = 0; kTimerNames[i]; ++i)
@@ -210,14 +213,14 @@ int finalize(bcm_plan* P, int op, int which0, int which1, int nparts, int first,
   FinalizeArgs a{P->at<double>(P->o_part[which0]), which1 >= 0 ? P->at<double>(P->o_part[which1]) : nullptr,
                  nparts, P->at<Scalars>(P->o_sc), op, first, publish ? P->mirror : nullptr,
                  publish ? ++P->mirror_seq : 0u};
-  HIPCHK(timed(P, cls_of("finalize", 0), s, [&] { return launch_finalize(a, s); }), "k_finalize");
+  HIPCHK(timed(P, cls_of(P, "finalize", 0), s, [&] { return launch_finalize(a, s); }), "k_finalize");
   return BCM_OK;
 }
 
 // Export the faces of an FP64 field (kc_ir without an update).
 int export64(bcm_plan* P, double* x, double* xf, hipStream_t s) {
   IrArgs<float> a{geom(P, P->n), x, nullptr, xf, 0.0};
-  HIPCHK(timed(P, cls_of("export", 0), s, [&] { return launch_ir<float>(P->n, a, s); }), "export faces");
+  HIPCHK(timed(P, cls_of(P, "export", 0), s, [&] { return launch_ir<float>(P->n, a, s); }), "export faces");
   return BCM_OK;
 }
 
@@ -233,7 +236,7 @@ int coarse_split(bcm_plan* P, const T* b_in, T* x_out, T* xf_out, hipStream_t s)
     ga.g = g;
     ga.lo = lo;
     ga.hi = hi;
-    HIPCHK(timed(P, cls_of("coarse", 0), s, [&] { return launch_g_step<T>(kind, n, ga, s); }),
+    HIPCHK(timed(P, cls_of(P, "coarse", 0), s, [&] { return launch_g_step<T>(kind, n, ga, s); }),
            "graph multigrid step");
     return BCM_OK;
   };
@@ -259,7 +262,7 @@ int coarse_split(bcm_plan* P, const T* b_in, T* x_out, T* xf_out, hipStream_t s)
                       std::max(P->o.coarse_iters, 64), P->at<double>(P->o_gw),
                       P->M->coarse.bottom_inv.empty() ? nullptr : P->at<const T>(P->o_ginv), P->g_lds,
                       P->g_lds_inv};
-    HIPCHK(timed(P, cls_of("coarse", 0), s, [&] { return launch_coarse_mg<T>(a, s); }), "k_coarse_mg");
+    HIPCHK(timed(P, cls_of(P, "coarse", 0), s, [&] { return launch_coarse_mg<T>(a, s); }), "k_coarse_mg");
     for (int g = S - 1; g >= 0 && !st; --g) {
       st = step(G_PROLONG, g, Ls[g].n);
       for (int k = 0; k < post && !st; ++k) st = sweep(g, false);
@@ -283,15 +286,18 @@ struct VLevels {
 // pre-smoother adds them (it reads nothing across faces itself: its iterate starts at zero),
 // and kc_rfix only after the last such level.
 // upd (level 0): the previous Krylov step's r update, applied by this launch to b (= r).
+// n_pq > 0: alpha is still to be formed from that many partial sums of <p, q>.
 template <typename T>
-int presmooth(bcm_plan* P, int l, hipStream_t s, const UpdateArgs<T>* upd = nullptr) {
+int presmooth(bcm_plan* P, int l, hipStream_t s, const UpdateArgs<T>* upd = nullptr, int n_pq = 0) {
   const VLevels<T> V{P};
   const int NL = P->n >> l;
   SmoothArgs<T> sa{};
   if (upd) {
     sa.upd_q = upd->q;
-    sa.upd_sc = upd->sc;
+    sa.upd_sc = P->at<Scalars>(P->o_sc);
     sa.part_rr = P->at<double>(P->o_part[0]);
+    sa.part_pq = n_pq > 0 ? P->at<const double>(P->o_part[2]) : nullptr;
+    sa.n_pq = n_pq;
   }
   sa.g = geom(P, NL);
   sa.x = V.X(l);
@@ -306,7 +312,7 @@ int presmooth(bcm_plan* P, int l, hipStream_t s, const UpdateArgs<T>* upd = null
     sa.b_fixed = V.B(l);
     sa.rfx_hscale = geom(P, NL * 2).hscale;
   }
-  HIPCHK(timed(P, cls_of(upd ? "preupd" : "presmooth", NL), s, [&] { return launch_smooth<T>(NL, sa, s); }),
+  HIPCHK(timed(P, cls_of(P, upd ? "preupd" : "presmooth", NL), s, [&] { return launch_smooth<T>(NL, sa, s); }),
          "kc_smooth (pre)");
   return BCM_OK;
 }
@@ -319,9 +325,10 @@ int presmooth(bcm_plan* P, int l, hipStream_t s, const UpdateArgs<T>* upd = null
 // upd: the previous Krylov step's r update, applied by the level-0 pre-smoother (which needs
 // nlev >= 2), after which after_pre0(stop) runs (the convergence check); stop = true ends the
 // V-cycle there.
+// n_zr: receives the number of partial sums of <z, r> (and <z, q>).
 template <typename T, class Hook, class After>
-int vcycle(bcm_plan* P, const T* q_dot, hipStream_t s, Hook&& before_coarse, const UpdateArgs<T>* upd,
-           After&& after_pre0, bool& stop) {
+int vcycle(bcm_plan* P, const T* q_dot, hipStream_t s, Hook&& before_coarse, const UpdateArgs<T>* upd, int n_pq,
+           After&& after_pre0, bool& stop, int* n_zr) {
   const int L = P->nlev;
   const VLevels<T> V{P};
   auto X = [&](int l) { return V.X(l); };
@@ -331,10 +338,10 @@ int vcycle(bcm_plan* P, const T* q_dot, hipStream_t s, Hook&& before_coarse, con
   stop = false;
   for (int l = 0; l < L - 1; ++l) {
     const int NL = P->n >> l;
-    if (const int st = presmooth<T>(P, l, s, l == 0 ? upd : nullptr)) return st;
+    if (const int st = presmooth<T>(P, l, s, l == 0 ? upd : nullptr, l == 0 ? n_pq : 0)) return st;
     if (l == L - 2) {
       RestrictFixArgs<T> ra{geom(P, NL), F(0, l), B(l + 1)};
-      HIPCHK(timed(P, cls_of("restrict", NL), s, [&] { return launchc_rfix<T>(NL, ra, s); }), "kc_rfix");
+      HIPCHK(timed(P, cls_of(P, "restrict", NL), s, [&] { return launchc_rfix<T>(NL, ra, s); }), "kc_rfix");
     }
     if (l == 0) {
       if (const int st = after_pre0(stop)) return st;
@@ -352,12 +359,12 @@ int vcycle(bcm_plan* P, const T* q_dot, hipStream_t s, Hook&& before_coarse, con
                        P->M->coarse.bottom_inv.empty() ? nullptr : P->at<const T>(P->o_ginv), P->g_lds,
                       P->g_lds_inv};
     if (const int st = before_coarse(&ga)) return st;  // may hand it a vector update to carry
-    HIPCHK(timed(P, cls_of("coarse", 0), s, [&] { return launch_coarse_mg<T>(ga, s); }), "k_coarse_mg");
+    HIPCHK(timed(P, cls_of(P, "coarse", 0), s, [&] { return launch_coarse_mg<T>(ga, s); }), "k_coarse_mg");
   } else {
     if (const int st = before_coarse(nullptr)) return st;
     CoarseArgs<T> ca{P->at<const CubeMeta>(P->o_meta), P->nc, double(P->n), B(L - 1), X(L - 1),
                      F(1, L - 1), P->at<double>(P->o_cw), o.coarse_iters};
-    HIPCHK(timed(P, cls_of("coarse", 0), s, [&] { return launch_coarse<T>(ca, s); }), "k_coarse");
+    HIPCHK(timed(P, cls_of(P, "coarse", 0), s, [&] { return launch_coarse<T>(ca, s); }), "k_coarse");
   }
   for (int l = L - 2; l >= 0; --l) {
     const int NL = P->n >> l;
@@ -378,8 +385,9 @@ int vcycle(bcm_plan* P, const T* q_dot, hipStream_t s, Hook&& before_coarse, con
       sa.q_dot = q_dot;
       sa.part_zr = P->at<double>(P->o_part[0]);
       sa.part_zq = q_dot ? P->at<double>(P->o_part[1]) : nullptr;
+      sa.n_wg = n_zr;
     }
-    HIPCHK(timed(P, cls_of("postsmooth", NL), s, [&] { return launch_smooth<T>(NL, sa, s); }), "kc_smooth (post)");
+    HIPCHK(timed(P, cls_of(P, "postsmooth", NL), s, [&] { return launch_smooth<T>(NL, sa, s); }), "kc_smooth (post)");
   }
   return BCM_OK;
 }
@@ -422,7 +430,7 @@ int krylov(bcm_plan* P, T* x, bool x_zero, double thr, int max_iter, double hist
   UpdateArgs<T> ux{};
   bool pending = false, in_flight = false;
   auto launch_x = [&](hipStream_t on) {
-    return timed(P, cls_of("xupdate", 0), on, [&] { return launch_update<T>(ux, on); });
+    return timed(P, cls_of(P, "xupdate", 0), on, [&] { return launch_update<T>(ux, on); });
   };
   auto start_x = [&](bool beside, CoarseMGArgs<T>* carrier) -> int {
     if (!pending) return BCM_OK;
@@ -478,6 +486,18 @@ int krylov(bcm_plan* P, T* x, bool x_zero, double thr, int max_iter, double hist
   // never reads r again); if the solve goes on, the fused launch still applies the update and
   // skips the check (probed).  After the last allowed iteration the probe also serves.
   const bool fuse = P->nlev >= 2;
+  // With flexible CG the scalars in the middle of an iteration are formed by the launch that
+  // needs them, from its producer's partial sums: beta by the apply, alpha by the fused
+  // pre-smoother (n_pq partial sums wait for it; before any other reader of alpha a finalize
+  // forms it).
+  const bool lazy = flex && fuse;
+  int n_zr = 0, n_pq = 0;
+  auto settle = [&]() -> int {
+    if (n_pq == 0) return BCM_OK;
+    const int n = n_pq;
+    n_pq = 0;
+    return finalize(P, OP_PQ, 2, -1, n, 0, s);
+  };
   UpdateArgs<T> ur{};
   bool r_pending = false, probed = false;
   double rr_a = -1.0, rr_b = -1.0;  // the last two checked <r, r> (rr_b the latest)
@@ -510,10 +530,11 @@ int krylov(bcm_plan* P, T* x, bool x_zero, double thr, int max_iter, double hist
   // the pending r update on its own (probe: only its <r, r>), with per-cube partials
   auto update_alone = [&](int it, bool probe, bool& stop) -> int {
     UpdateArgs<T> a = ur;
+    if (const int st = settle()) return st;
     a.part_sel = probe ? 3 : 1;
     r_pending = probe;
     probed = probe;
-    HIPCHK(timed(P, cls_of(probe ? "rprobe" : "update", 0), s, [&] { return launch_update<T>(a, s); }),
+    HIPCHK(timed(P, cls_of(P, probe ? "rprobe" : "update", 0), s, [&] { return launch_update<T>(a, s); }),
            "k_update");
     return check(it, P->nc, stop);
   };
@@ -533,8 +554,9 @@ int krylov(bcm_plan* P, T* x, bool x_zero, double thr, int max_iter, double hist
     const bool first = !fcg || (it == 0 && !(flex && carry));  // no direction to orthogonalise against
     int st = vcycle<T>(P, (flex && !first) ? q : nullptr, s,
                        [&](CoarseMGArgs<T>* carrier) { return start_x(true, carrier); },
-                       r_pending ? &ur : nullptr,
+                       r_pending ? &ur : nullptr, n_pq,
                        [&](bool& stop_) -> int {
+                         n_pq = 0;  // (the pre-smoother has formed alpha)
                          if (!r_pending) return BCM_OK;
                          r_pending = false;
                          if (probed) {  // checked already
@@ -543,17 +565,22 @@ int krylov(bcm_plan* P, T* x, bool x_zero, double thr, int max_iter, double hist
                          }
                          return check(it - 1, nparts, stop_);
                        },
-                       stop);
+                       stop, &n_zr);
     if (st) return finish(st);
     if (stop) break;
-    if ((st = finalize(P, OP_ZRZQ, 0, (flex && !first) ? 1 : -1, nparts, first, s))) return finish(st);
+    if (!lazy && (st = finalize(P, OP_ZRZQ, 0, (flex && !first) ? 1 : -1, nparts, first, s))) return finish(st);
     if ((st = join_x())) return finish(st);
     ApplyArgs<T> aa{geom(P, NL), z, P->at<T>(P->o_zf[1]), p, P->at<T>(P->o_pfk[P->pf_cur]),
-                    P->at<T>(P->o_pfk[P->pf_cur ^ 1]), q, P->at<const Scalars>(P->o_sc),
-                    first ? 1 : 0, P->at<double>(P->o_part[2])};
-    HIPCHK(timed(P, cls_of("apply", NL), s, [&] { return launch_apply<T>(NL, aa, s); }), "kc_apply");
+                    P->at<T>(P->o_pfk[P->pf_cur ^ 1]), q, P->at<Scalars>(P->o_sc),
+                    first ? 1 : 0, P->at<double>(P->o_part[2]),
+                    lazy ? P->at<const double>(P->o_part[0]) : nullptr, P->at<const double>(P->o_part[1]), n_zr,
+                    &n_pq};
+    HIPCHK(timed(P, cls_of(P, "apply", NL), s, [&] { return launch_apply<T>(NL, aa, s); }), "kc_apply");
     P->pf_cur ^= 1;
-    if ((st = finalize(P, OP_PQ, 2, -1, nparts, 0, s))) return finish(st);
+    if (!lazy) {
+      n_pq = 0;
+      if ((st = finalize(P, OP_PQ, 2, -1, nparts, 0, s))) return finish(st);
+    }
     if (!fcg) {  // stationary iteration: x += z, r -= A z  (alpha = 1)
       if ((st = finalize(P, OP_PQ, 0, -1, nparts, 0, s))) return finish(st);  // alpha = zr / zr
     }
@@ -583,7 +610,7 @@ int residual64(bcm_plan* P, const double* p, const double* b, TO* r, double rsca
   }
   Resid64Args<TO> ra{geom(P, NL), p, P->at<const double>(P->o_pf), b, r,
                      P->at<double>(P->o_part[0]), P->at<double>(P->o_part[1]), rscale};
-  HIPCHK(timed(P, cls_of("resid64", 0), s, [&] { return launch_resid64<TO>(NL, ra, s); }), "kc_resid64");
+  HIPCHK(timed(P, cls_of(P, "resid64", 0), s, [&] { return launch_resid64<TO>(NL, ra, s); }), "kc_resid64");
   return finalize(P, OP_BB, 0, 1, partials_of(NL, P->nc), 0, s);
 }
 
@@ -728,7 +755,7 @@ int poisson(bcm_plan* P, const double* b, double* p, bool use_guess, bcm_report*
         return fail(st);
       IrArgs<float> ia{geom(P, P->n), p, d, P->at<double>(P->o_pf), 1.0 / rscale, p_unwritten ? 1 : 0,
                        last.p, last.sc, last.p ? last.x_zero : 0};
-      HIPCHK(timed(P, cls_of("ir", 0), s, [&] { return launch_ir<float>(P->n, ia, s); }), "kc_ir");
+      HIPCHK(timed(P, cls_of(P, "ir", 0), s, [&] { return launch_ir<float>(P->n, ia, s); }), "kc_ir");
       p_unwritten = false;
       faces_ok = true;  // kc_ir exports the faces of the updated p
       unchecked = true;
@@ -780,7 +807,7 @@ int project_impl(bcm_plan* P, const bcm_project_in* in, bcm_project_out* out, bc
   // 16^3 kernels: force and store u* only in cubes that hold some alpha != 0; the others pass
   // u~ on
   fa.body = NL == 16 ? P->at<uint8_t>(P->o_body) : nullptr;
-  HIPCHK(timed(P, cls_of("force", 0), s, [&] { return launch_force<TF>(NL, fa, s); }), "k_force");
+  HIPCHK(timed(P, cls_of(P, "force", 0), s, [&] { return launch_force<TF>(NL, fa, s); }), "k_force");
   double* p = out->p;
   int st = BCM_OK;
   if (!p_given) {
@@ -795,7 +822,7 @@ int project_impl(bcm_plan* P, const bcm_project_in* in, bcm_project_out* out, bc
     da.U_in = in->U_in;
     da.inv_c = 1.0 / c;
     da.b = P->at<double>(P->o_b64);
-    HIPCHK(timed(P, cls_of("div", 0), s, [&] { return launch_div<TF>(NL, da, s); }), "k_div");
+    HIPCHK(timed(P, cls_of(P, "div", 0), s, [&] { return launch_div<TF>(NL, da, s); }), "k_div");
     bool guess = false;
     if (in->p0) {
       if (in->p0 != p)
@@ -826,7 +853,7 @@ int project_impl(bcm_plan* P, const bcm_project_in* in, bcm_project_out* out, bc
   ca.body = fa.body;
   ca.U_in = in->U_in;
   ca.c = c;
-  HIPCHK(timed(P, cls_of("correct", 0), s, [&] { return launch_correct<TF>(NL, ca, s); }), "k_correct");
+  HIPCHK(timed(P, cls_of(P, "correct", 0), s, [&] { return launch_correct<TF>(NL, ca, s); }), "k_correct");
   return st;
 }
 
@@ -846,14 +873,14 @@ int adjoint_impl(bcm_plan* P, const bcm_adjoint_in* in, bcm_adjoint_out* out, bc
     for (int d = 0; d < 3; ++d) ea.u[d] = gun[d];
     ea.uf = vf;
     ea.body = P->at<uint8_t>(P->o_body);
-    HIPCHK(timed(P, cls_of("export", 0), s, [&] { return launch_force<TF>(NL, ea, s); }), "export g_u faces");
+    HIPCHK(timed(P, cls_of(P, "export", 0), s, [&] { return launch_force<TF>(NL, ea, s); }), "export g_u faces");
   } else {
     ExportArgs<TF, TF> ea{};
     ea.g = geom(P, NL);
     ea.xf = vf;
     ea.comp_faces = 1;
     for (int d = 0; d < 3; ++d) ea.x3[d] = gun[d];
-    HIPCHK(timed(P, cls_of("export", 0), s, [&] { return launch_export<TF, TF>(NL, ea, s); }), "export g_u faces");
+    HIPCHK(timed(P, cls_of(P, "export", 0), s, [&] { return launch_export<TF, TF>(NL, ea, s); }), "export g_u faces");
   }
   AdjGpArgs<TF> ga{};
   ga.g = geom(P, NL);
@@ -862,7 +889,7 @@ int adjoint_impl(bcm_plan* P, const bcm_adjoint_in* in, bcm_adjoint_out* out, bc
   ga.gp_in = in->g_p;
   ga.c = c;
   ga.out = P->at<double>(P->o_b64);
-  HIPCHK(timed(P, cls_of("adj_gp", 0), s, [&] { return launch_adj_gp<TF>(NL, ga, s); }), "k_adj_gp");
+  HIPCHK(timed(P, cls_of(P, "adj_gp", 0), s, [&] { return launch_adj_gp<TF>(NL, ga, s); }), "k_adj_gp");
   double* lam = P->at<double>(P->o_lam);
   int st = poisson(P, P->at<const double>(P->o_b64), lam, false, rep, s);
   if (st < 0) return st;
@@ -887,7 +914,7 @@ int adjoint_impl(bcm_plan* P, const bcm_adjoint_in* in, bcm_adjoint_out* out, bc
   ra.accumulate = out->accumulate != 0;
   ra.inv_c = 1.0 / c;
   ra.part_gU = P->at<double>(P->o_part[0]);
-  HIPCHK(timed(P, cls_of("adj_rhs", 0), s, [&] { return launch_adj_rhs<TF>(NL, ra, s); }), "k_adj_rhs");
+  HIPCHK(timed(P, cls_of(P, "adj_rhs", 0), s, [&] { return launch_adj_rhs<TF>(NL, ra, s); }), "k_adj_rhs");
   if (const int e = finalize(P, OP_GU, 0, -1, adj_rhs_parts(NL, P->nc), 0, s)) return e;
   Scalars hs{};
   if (const int e = read_scalars(P, &hs, s)) return e;
@@ -956,7 +983,7 @@ int momentum_impl(bcm_plan* P, const bcm_momentum_in* in, bcm_momentum_out* out,
   if (rep) rep->history_len = 0;
   auto launch = [&](int mode) {  // timer class "momentum": the passes over H (explicit step or
                                  // Crank-Nicolson sweep); "momentum_start": the CN start
-    const int cls = cls_of(mode == MOM_CN_START ? "momentum_start" : "momentum", 0);
+    const int cls = cls_of(P, mode == MOM_CN_START ? "momentum_start" : "momentum", 0);
     return timed(P, cls, s, [&] { return launch_mom<TF>(NL, mode, ma, grid, s); });
   };
   if (in->scheme != BCM_CN) {
@@ -1060,7 +1087,7 @@ int ib_force_impl(bcm_plan* P, const bcm_particles* pt, const void* const u_tild
   a.Fp = Fp;
   a.errors = P->at<unsigned int>(P->o_iberr);
   HIPCHK(launch_zero_u32(a.errors, s), "zero the skip counter");
-  HIPCHK(timed(P, cls_of("ib", 0), s, [&] { return launch_ib_force<TF>(a, s); }), "k_ib_force");
+  HIPCHK(timed(P, cls_of(P, "ib", 0), s, [&] { return launch_ib_force<TF>(a, s); }), "k_ib_force");
   unsigned int skipped = 0;
   HIPCHK(hipMemcpyAsync(&skipped, a.errors, sizeof(skipped), hipMemcpyDeviceToHost, s), "skip counter readback");
   HIPCHK(hipStreamSynchronize(s), "stream synchronize");
@@ -1705,10 +1732,10 @@ int bcm_compress(bcm_plan* P, const double* d_field, double step, void* d_stream
   a.stream = d_stream;
   a.capacity = capacity;
   const int units = (P->nc + col_cpb(P->n) - 1) / col_cpb(P->n);
-  HIPCHK(timed(P, cls_of("codec", 0), s, [&] { return launch_wc_encode(P->n, a, std::min(units, kWcGrid), s); }),
+  HIPCHK(timed(P, cls_of(P, "codec", 0), s, [&] { return launch_wc_encode(P->n, a, std::min(units, kWcGrid), s); }),
          "k_wc_encode");
   HIPCHK(launch_wc_header(a, s), "k_wc_header");
-  HIPCHK(timed(P, cls_of("codec", 0), s, [&] { return launch_wc_pack(P->n, a, std::min((P->nc + 3) / 4, 2048), s); }),
+  HIPCHK(timed(P, cls_of(P, "codec", 0), s, [&] { return launch_wc_pack(P->n, a, std::min((P->nc + 3) / 4, 2048), s); }),
          "k_wc_pack");
   unsigned long long back[2];
   if ((st = codec_result(P, back, s))) return st;
@@ -1746,7 +1773,7 @@ int bcm_decompress(bcm_plan* P, const void* d_stream, size_t bytes, double* d_fi
   a.data_bytes = bytes - head;
   a.field_out = d_field;
   const int units = (P->nc + col_cpb(P->n) - 1) / col_cpb(P->n);
-  HIPCHK(timed(P, cls_of("codec", 0), s, [&] { return launch_wc_decode(P->n, a, std::min(units, kWcGrid), s); }),
+  HIPCHK(timed(P, cls_of(P, "codec", 0), s, [&] { return launch_wc_decode(P->n, a, std::min(units, kWcGrid), s); }),
          "k_wc_decode");
   HIPCHK(launch_wc_verdict(a, s), "k_wc_verdict");
   unsigned long long back[2];
@@ -1800,7 +1827,7 @@ int bcm_apply_laplacian(bcm_plan* P, const double* d_p, double* d_Ap, void* stre
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = export64(P, const_cast<double*>(d_p), P->at<double>(P->o_pf), s))) return st;
   Resid64Args<double> ra{geom(P, P->n), d_p, P->at<const double>(P->o_pf), nullptr, d_Ap, nullptr, nullptr, 1.0};
-  HIPCHK(timed(P, cls_of("resid64", 0), s, [&] { return launch_resid64<double>(P->n, ra, s); }), "kc_resid64 (apply)");
+  HIPCHK(timed(P, cls_of(P, "resid64", 0), s, [&] { return launch_resid64<double>(P->n, ra, s); }), "kc_resid64 (apply)");
   return BCM_OK;
 }
 
