@@ -741,12 +741,13 @@ int poisson(bcm_plan* P, const double* b, double* p, bool use_guess, bcm_report*
       // Reduce the residual by inner_tol, or only by what is still missing to reach tol (with a
       // factor 0.3 of margin), whichever is the weaker requirement.  But when one inner solve
       // can reach tol by going further than inner_tol, and that lies well above what FP32
-      // rounding left of the previous one, let it (factor 0.5 of margin, as in FP64 mode): a
-      // further refinement step costs two passes in FP64 for one or two iterations.
+      // rounding left of the previous one, let it (factor 0.6 of margin, which that rounding, at
+      // most a fifth of the target, cannot use up): a further refinement step costs two passes
+      // in FP64 for one or two iterations.
       const double miss = o.tol * std::sqrt(bb / rr);
       const double rounding = outer > 0 ? std::sqrt(std::max(rr - rr_est, 0.0) / rr_before) : 1.0;
-      const bool reach = 0.5 * miss >= 0.01 * o.inner_tol && 0.5 * miss >= 4.0 * rounding;
-      const double red_target = reach ? std::min(0.5 * miss, 0.1) : std::max(o.inner_tol, std::min(0.3 * miss, 0.1));
+      const bool reach = 0.6 * miss >= 0.01 * o.inner_tol && 0.6 * miss >= 5.0 * rounding;
+      const double red_target = reach ? std::min(0.6 * miss, 0.1) : std::max(o.inner_tol, std::min(0.3 * miss, 0.1));
       rr_before = rr;
       const double thr = red_target * red_target * rr * rscale * rscale;
       UpdateArgs<float> last{};  // the inner solve's last x update, folded into kc_ir
