@@ -43,3 +43,21 @@ def test_solves_reach_the_tolerance(name, opts):
     if tol <= 1e-10:
         assert rel_err(host(p), host(p3)) <= 1e-7
         assert rel_err(host(p), fv.solve(b)) <= 1e-7
+
+
+@pytest.mark.parametrize("n", [2, 4, 8])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_solves_that_converge_at_once(n, precision):
+    """A constant right-hand side on one open cube leaves a handful of unknowns by symmetry: CG
+    ends in a few iterations with a residual that falls to rounding from one check to the next,
+    which no earlier check predicts.  The cube's condition number (3 pi^2 against 12 n^2, the
+    ghost at half a cell) times the solve tolerance bounds the error of p."""
+    m = uniform_mesh((1, 1, 1), 0.5, n, OPEN_BC)
+    fv = FVMesh(m)
+    plan = plan_for(m, precision)
+    b = np.full(m.n_cells, 3.0)
+    p, rep = plan.poisson_solve(dev(b))
+    assert rep.status == 0 and rep.final_rel_res <= 1e-10
+    assert rel_err(host(p), fv.solve(b)) <= n * n * 1e-10
+    p2, rep2 = plan.poisson_solve(dev(b))
+    assert np.array_equal(host(p), host(p2)) and rep2.history == rep.history
