@@ -528,14 +528,16 @@ template <typename T, int NL, bool POST, bool ML, bool TRI = false, bool UPD = f
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? (NL == 8 ? 4 : 3) : 2) void kc_smooth(SmoothArgs<T> a) {
   using C = Col<NL>;
   constexpr bool PF = sizeof(T) == 4 || NL < 16;
-  // sweep form (same update order): shifted columns before restriction; in FP32 after the
-  // trilinear prolongation or at 16^3 the paired form (fewer registers), else the masked form
-  constexpr int SWEEP = !POST ? 2 : (sizeof(T) == 4 && (TRI || NL == 16) ? 1 : 0);
+  // sweep form (same update order): shifted columns before restriction; the paired form after
+  // the trilinear prolongation and at 16^3 in FP32, else the masked form.  Paired issues half of
+  // the masked form's LDS reads (64 cubes of 16^3 in FP64 1140 -> 1095 us a projection, 1024
+  // cubes 2612 -> 2558 us).
+  constexpr int SWEEP = !POST ? 2 : (TRI || (sizeof(T) == 4 && NL == 16) ? 1 : 0);
   // the halo-free tile of the 16^3 pre-smoother (plane pitch ZP words)
   constexpr bool ZL = !POST && NL == 16 && !ML;
-  // the paired form at 16^3 (the FP32 trilinear post-smoother): rows of 32 words and planes
-  // of 592, so that lanes one plane apart use other banks of each half-wavefront
-  using CT = std::conditional_t<SWEEP == 1 && NL == 16, Col<NL, 32, 592>, Col<NL>>;
+  // the paired form at 16^3 in FP32: rows of 32 words and planes of 592, so that lanes one plane
+  // apart use other banks of each half-wavefront (in FP64 that tile would halve the occupancy)
+  using CT = std::conditional_t<SWEEP == 1 && NL == 16 && sizeof(T) == 4, Col<NL, 32, 592>, Col<NL>>;
   constexpr int ZP = C::N2 + 64, TSL = ZL ? NL * ZP : CT::TS;
   // pre-smoother below the finest level: the finer level's face correction is applied here
   constexpr bool RFX = !POST && NL < 16;
