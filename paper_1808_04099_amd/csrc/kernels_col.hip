@@ -505,13 +505,14 @@ __device__ __forceinline__ void tri_column(const T* ct, const LaneC<NL>& L, T (&
 //
 // The sweeps keep the column x (b in bv) in registers, the x/y neighbours in the LDS tile and
 // the z halo in zlo / zhi, with one barrier per colour.  In a column the colour of cell k
-// alternates, in phase with the lane's (i + j) parity; three forms of the same update order
-// differ in how a lane reaches its cells of one colour:
-//   masked:  every k, with the lanes of the other colour idle;
-//   paired:  one cell of each pair (2n, 2n + 1), picked per lane by selects;
-//   shifted: the column is copied into slots shifted by the parity (slot s = k + par + 1, the
-//            z halo in slots par and NL + par + 1), so that one colour sits in the same slots
-//            on every lane.
+// alternates, in phase with the lane's (i + j) parity; two forms of the same update order
+// differ in how a lane reaches its cells of one colour (stepping through every cell with the lanes
+// of the other colour idle takes twice the LDS reads: in FP64 64 cubes of 16^3 1140 -> 1095 us a
+// projection without it, 1024 cubes 2612 -> 2558 us, 432 cubes of a two-level mesh 12.17 -> 12.10 ms):
+//   paired:  (post-smoothers) one cell of each pair (2n, 2n + 1), picked per lane by selects;
+//   shifted: (pre-smoothers) the column is copied into slots shifted by the parity (slot
+//            s = k + par + 1, the z halo in slots par and NL + par + 1), so that one colour sits
+//            in the same slots on every lane.
 // In the shifted and paired forms a lane of parity 1 works one plane away from its neighbours
 // of parity 0.  With (NL+2)-wide rows that puts lanes of a half-wavefront (the 32 lanes whose
 // 32-bit LDS accesses are served together) on the same bank.  At 16^3:
@@ -528,16 +529,11 @@ template <typename T, int NL, bool POST, bool ML, bool TRI = false, bool UPD = f
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? (NL == 8 ? 4 : 3) : 2) void kc_smooth(SmoothArgs<T> a) {
   using C = Col<NL>;
   constexpr bool PF = sizeof(T) == 4 || NL < 16;
-  // sweep form (same update order): shifted columns before restriction; the paired form after
-  // the trilinear prolongation and at 16^3 in FP32, else the masked form.  Paired issues half of
-  // the masked form's LDS reads (64 cubes of 16^3 in FP64 1140 -> 1095 us a projection, 1024
-  // cubes 2612 -> 2558 us).
-  constexpr int SWEEP = !POST ? 2 : (TRI || (sizeof(T) == 4 && NL == 16) ? 1 : 0);
   // the halo-free tile of the 16^3 pre-smoother (plane pitch ZP words)
   constexpr bool ZL = !POST && NL == 16 && !ML;
   // the paired form at 16^3 in FP32: rows of 32 words and planes of 592, so that lanes one plane
   // apart use other banks of each half-wavefront (in FP64 that tile would halve the occupancy)
-  using CT = std::conditional_t<SWEEP == 1 && NL == 16 && sizeof(T) == 4, Col<NL, 32, 592>, Col<NL>>;
+  using CT = std::conditional_t<POST && NL == 16 && sizeof(T) == 4, Col<NL, 32, 592>, Col<NL>>;
   constexpr int ZP = C::N2 + 64, TSL = ZL ? NL * ZP : CT::TS;
   // pre-smoother below the finest level: the finer level's face correction is applied here
   constexpr bool RFX = !POST && NL < 16;
@@ -770,24 +766,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? (NL == 8 ? 4 : 3) : 2) void k
 #pragma unroll
       for (int k = 0; k < NL; ++k) q[k] = ld_nt(a.q_dot + (size_t)ce * C::N3 + k * C::N2 + L.l);
     }
-    if constexpr (SWEEP == 0) {
-    for (int sw = 0; sw < a.sweeps; ++sw) {
-  #pragma unroll
-      for (int col = 0; col < 2; ++col) {
-        const int colour = POST ? (col ^ 1) : col;
-  #pragma unroll
-        for (int k = 0; k < NL; ++k) {
-          if (((i + j + k) & 1) != colour) continue;
-          const int cc = CT::tix(L.s, i, j, k);
-          const T sum = nbsum<NL, T, CT>(tile, x, k, cc, zlo, zhi);
-          const T id = k == 0 ? i0 : (k == NL - 1 ? il : im);
-          x[k] = (sum - h2 * bv[k]) * id;
-          tile[cc] = x[k];
-        }
-        __syncthreads();
-      }
-    }
-    } else if constexpr (SWEEP == 1) {
+    if constexpr (POST) {
     const int par = (i + j) & 1;
     for (int sw = 0; sw < a.sweeps; ++sw) {
   #pragma unroll
