@@ -187,9 +187,13 @@ void build_level(CoarseLevel& L, const std::vector<Key>& keys, const int dims[3]
   }
   L.order.clear();
   L.color_off.assign(1, 0);
+  L.wide_off.clear();
   for (int c = 0; c < ncol; ++c) {
-    for (int t = 0; t < n; ++t)
-      if (colour[t] == c) L.order.push_back(t);
+    for (int wide = 0; wide < 2; ++wide) {
+      if (wide) L.wide_off.push_back(int(L.order.size()));
+      for (int t = 0; t < n; ++t)
+        if (colour[t] == c && (L.row[t + 1] - L.row[t] > kRow) == bool(wide)) L.order.push_back(t);
+    }
     L.color_off.push_back(int(L.order.size()));
   }
 }
@@ -419,6 +423,9 @@ bool build_coarse_hierarchy(const HostMesh& M, CoarseHierarchy& H, int max_level
     }
     if (g == 0) L.perm = id;
   }
+  H.wide = 0;
+  for (size_t g = 0; g < H.levels.size(); ++g)
+    if (H.levels[g].W > kRow) H.wide = int(g) + 1;
   H.bottom_inv = dense_inverse_transposed(H.levels.back());
   H.ok = true;
   return true;

@@ -16,6 +16,8 @@ struct CoarseLevel {
   std::vector<double> vol;            // relative node volume
   std::vector<int32_t> order;         // nodes grouped by colour
   std::vector<int32_t> color_off;     // colour c = order[color_off[c] .. color_off[c+1])
+  std::vector<int32_t> wide_off;      // its nodes with more than kRow couplings: the last ones,
+                                      // order[wide_off[c] .. color_off[c+1])
   std::vector<int32_t> parent;        // node -> node of the next coarser level
   std::vector<int32_t> child_row, child;  // (this level) node -> children on the finer level
   std::vector<double> child_w;        // restriction weights (volume fractions, sum 1)
@@ -34,11 +36,17 @@ struct CoarseLevel {
   double uval = 0.0;
 };
 
+// Couplings of an interior node of a lattice.  Next to a 2:1 interface a node has up to 24, but
+// only one in twenty has more than six: the wide ones are sorted to the end of their colour, and
+// the other nodes' passes do not read the slots past the sixth.
+constexpr int kRow = 6;
+
 // The last graph level is solved directly (dense inverse) when it has at most this many nodes.
 constexpr int kBottomDirectMax = 64;
 
 struct CoarseHierarchy {
   bool ok = false;
+  int wide = 0;                       // number of leading levels with wide rows
   std::vector<CoarseLevel> levels;    // levels[0] = the one-cell-per-cube graph
   std::vector<double> bottom_inv;     // [n][n] transposed inverse of the last level, or empty
 };
@@ -51,6 +59,7 @@ template <typename T>
 struct GLevel {
   int n, ncol, W, CW;
   int color_off[9];         // up to 8 colours, contiguous node ranges
+  int wide_off[8];          // per colour: first node with more than kRow couplings
   int lds_x, lds_b, lds_r;  // byte offsets in the kernel's dynamic LDS, or -1
   const int32_t* col;       // [W][n]
   const T* val;             // [W][n]
@@ -79,6 +88,7 @@ struct CoarseMGArgs {
   int start;                // first level this workgroup solves: 0, or the first level below
                             // the ones smoothed by the multi-workgroup kernels (its b and x
                             // then come from and go to the levels' global buffers)
+  int wide;                 // some level solved here has wide rows
   int cycles, pre, post, bottom_iters;
   double* w;                // CG work space for the bottom level (4 * n_last doubles)
   const T* binv;            // transposed inverse of the bottom operator, or nullptr (CG)
@@ -103,7 +113,7 @@ template <typename T>
 struct GStepArgs {
   const GLevel<T>* lev;     // device array of levels (global buffers)
   int g;                    // level
-  int lo, hi;               // node range (one colour) of a smoothing pass
+  int lo, hi, wide;         // node range (one colour) of a smoothing pass, first wide node in it
   const T* b_in;            // gather: one-cell-per-cube right-hand side (cube order)
   T* x_out;                 // scatter: solution (cube order)
   T* xf_out;                // and its face buffer

@@ -259,6 +259,58 @@ __device__ __forceinline__ void g_pass6(const GLevel<T>& L, int lo, int hi) {
   }
 }
 
+// Nodes [lo, hi) of one colour of a level with wide rows: N slots of a row, U nodes per lane per
+// round, all their coupling loads issued before any of them is used (a longer row goes on one
+// slot at a time).  Lane `lane` of `lanes`.
+template <typename T, bool RESID, int N, int U>
+__device__ __forceinline__ void g_rows(const GLevel<T>& L, T* x, int lo, int hi, int lane, int lanes) {
+  for (int base = lo + lane; base < hi; base += U * lanes) {
+    int col[U][N];
+    T val[U][N], bb[U], dg[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = base + u * lanes, ii = i < hi ? i : lo;
+#pragma unroll
+      for (int w = 0; w < N; ++w) {
+        const size_t o = size_t(N <= kRow || w < L.W ? w : 0) * L.n + ii;
+        col[u][w] = L.col[o];
+        val[u][w] = L.val[o];
+      }
+      bb[u] = L.b[ii];
+      dg[u] = L.diag[ii];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = base + u * lanes;
+      if (i >= hi) continue;
+      T acc = T(0);
+#pragma unroll
+      for (int w = 0; w < N; ++w)
+        if (N <= kRow || w < L.W) acc += val[u][w] * x[col[u][w]];
+      if constexpr (N > kRow)
+        for (int w = N; w < L.W; ++w) acc += L.val[size_t(w) * L.n + i] * x[L.col[size_t(w) * L.n + i]];
+      if (RESID)
+        L.r[i] = bb[u] - dg[u] * x[i] - acc;
+      else
+        x[i] = (bb[u] - acc) / dg[u];
+    }
+  }
+}
+
+// One colour: its narrow nodes on the first lanes, its wide ones (at most a quarter of the lanes
+// at a time) on the last wavefronts, side by side.  A pass is bound by the latency of its rows
+// rather than by their bytes.  With every node reading all the slots of the widest row one after
+// another, and x through generic pointers, one workgroup took 248 us in FP64 and 179 us in FP32
+// for a V-cycle on the 4856 + 2504 + 432 nodes of a two-level mesh; now 118 us and 84 us.
+template <typename T, bool RESID>
+__device__ __forceinline__ void g_pass(const GLevel<T>& L, T* x, int c) {
+  constexpr int U = sizeof(T) == 4 ? 2 : 1;  // (one more each spills)
+  const int lo = L.color_off[c], mid = L.wide_off[c], hi = L.color_off[c + 1], t = threadIdx.x;
+  const int wide = min(256, (hi - mid + 63) & ~63), narrow = 1024 - wide;
+  if (t < narrow) g_rows<T, RESID, kRow, U>(L, x, lo, mid, t, narrow);
+  else g_rows<T, RESID, 15, 1>(L, x, mid, hi, t - narrow, wide);
+}
+
 // Packed rows held in registers: lane t owns nodes t + 1024 k (k < K) of a level with at most
 // 1024 K nodes, so that its sweeps and residual read the rows once per kernel, not per pass
 // (the passes of one workgroup are bound by how fast its CU brings rows in: 56 bytes per node
@@ -357,6 +409,22 @@ __device__ void g_residual(const GLevel<T>& L) {
     for (int i = threadIdx.x; i < L.n; i += blockDim.x)
       L.r[i] = L.b[i] - L.diag[i] * L.x[i] - g_offdiag(L, L.x, i);
   }
+  __syncthreads();
+}
+
+// The same for levels with wide rows (x: the level's array, derived from the kernel's shared array
+// where it lies there, so that the gathers are LDS instructions rather than generic ones).
+template <typename T>
+__device__ __forceinline__ void g_smooth_wide(const GLevel<T>& L, T* x, int sweeps, bool forward) {
+  for (int s = 0; s < sweeps; ++s)
+    for (int cc = 0; cc < L.ncol; ++cc) {
+      g_pass<T, false>(L, x, forward ? cc : L.ncol - 1 - cc);
+      __syncthreads();
+    }
+}
+template <typename T>
+__device__ __forceinline__ void g_residual_wide(const GLevel<T>& L, T* x) {
+  for (int c = 0; c < L.ncol; ++c) g_pass<T, true>(L, x, c);
   __syncthreads();
 }
 
@@ -479,7 +547,9 @@ __device__ __forceinline__ void coarse_side_update(const CoarseMGArgs<T>& a) {
     a.xu_x[e] = (a.xu_zero ? T(0) : a.xu_x[e]) + al * a.xu_p[e];
 }
 
-template <typename T>
+// WIDE: some level has wide rows (2:1 interfaces).  A kernel of its own, without the rows in
+// registers, which the wide passes would make spill.
+template <typename T, bool WIDE>
 __global__ __launch_bounds__(1024) void k_coarse_mg(CoarseMGArgs<T> a) {
   if (blockIdx.x > 0) {  // the side update (only launched with xu_n > 0)
     coarse_side_update(a);
@@ -532,9 +602,9 @@ __global__ __launch_bounds__(1024) void k_coarse_mg(CoarseMGArgs<T> a) {
   constexpr int K0 = sizeof(T) == 4 ? 8 : 4;
   GRows<T, K0> R0;
   GRows<T, 1> R1, R2;
-  const bool c0 = S + 1 < G && lv[S].pcol && lv[S].n <= K0 * 1024 && in_lds(S);
-  const bool c1 = sizeof(T) == 4 && S + 2 < G && lv[S + 1].pcol && lv[S + 1].n <= 1024 && in_lds(S + 1);
-  const bool c2 = sizeof(T) == 4 && S + 3 < G && lv[S + 2].pcol && lv[S + 2].n <= 1024 && in_lds(S + 2);
+  const bool c0 = !WIDE && S + 1 < G && lv[S].pcol && lv[S].n <= K0 * 1024 && in_lds(S);
+  const bool c1 = !WIDE && sizeof(T) == 4 && S + 2 < G && lv[S + 1].pcol && lv[S + 1].n <= 1024 && in_lds(S + 1);
+  const bool c2 = !WIDE && sizeof(T) == 4 && S + 3 < G && lv[S + 2].pcol && lv[S + 2].n <= 1024 && in_lds(S + 2);
   if (c0) R0.load(lv[S]);
   if (c1) R1.load(lv[S + 1]);
   if (c2) R2.load(lv[S + 2]);
@@ -542,7 +612,13 @@ __global__ __launch_bounds__(1024) void k_coarse_mg(CoarseMGArgs<T> a) {
   for (int cy = 0; cy < (S == 0 ? a.cycles : 1); ++cy) {
     for (int g = S; g + 1 < G; ++g) {
       const GLevel<T>& L = lv[g];
-      if (g == S && c0) {
+      if (WIDE && L.W >= kRow && L.lds_x >= 0) {
+        g_smooth_wide(L, lds(L.lds_x), a.pre, true);
+        g_residual_wide(L, lds(L.lds_x));
+      } else if (WIDE && L.W >= kRow) {
+        g_smooth_wide(L, L.x, a.pre, true);
+        g_residual_wide(L, L.x);
+      } else if (g == S && c0) {
         R0.smooth(L, lds(L.lds_x), lds(L.lds_b), a.pre, true);
         R0.residual(L, lds(L.lds_x), lds(L.lds_b), lds(L.lds_r));
       } else if (g == S + 1 && c1) {
@@ -577,7 +653,11 @@ __global__ __launch_bounds__(1024) void k_coarse_mg(CoarseMGArgs<T> a) {
         g_prolong(F, lds(F.lds_x), lds(C.lds_x));
       else
         g_prolong(F, F.x, C.x);
-      if (g == S && c0)
+      if (WIDE && F.W >= kRow && F.lds_x >= 0)
+        g_smooth_wide(F, lds(F.lds_x), a.post, false);
+      else if (WIDE && F.W >= kRow)
+        g_smooth_wide(F, F.x, a.post, false);
+      else if (g == S && c0)
         R0.smooth(F, lds(F.lds_x), lds(F.lds_b), a.post, false);
       else if (g == S + 1 && c1)
         R1.smooth(F, lds(F.lds_x), lds(F.lds_b), a.post, false);
@@ -618,22 +698,36 @@ __global__ __launch_bounds__(256) void k_g_gather(GStepArgs<T> a) {
   L.x[i] = T(0);
 }
 
-// sum_w val[w][i] * x[col[w][i]] with every load of the row issued before use (W <= 16).
+// sum_w val[w][i] * x[col[w][i]] with every load of the row issued before use (W <= 16); the
+// slots past kRow only for wide nodes.
 template <typename T>
-__device__ __forceinline__ T g_row(const GLevel<T>& L, int i) {
+__device__ __forceinline__ T g_row(const GLevel<T>& L, int i, bool wide) {
   if (L.W > 16) return g_offdiag(L, L.x, i);
   int col[16];
   T val[16], xv[16];
-#pragma unroll
-  for (int w = 0; w < 16; ++w) {
+  auto load = [&](int w) {
     col[w] = w < L.W ? L.col[size_t(w) * L.n + i] : i;
     val[w] = w < L.W ? L.val[size_t(w) * L.n + i] : T(0);
+  };
+  auto value = [&](int w) { xv[w] = w < L.W ? L.x[col[w]] : T(0); };
+#pragma unroll
+  for (int w = 0; w < kRow; ++w) load(w);
+  if (wide)
+#pragma unroll
+    for (int w = kRow; w < 16; ++w) load(w);
+#pragma unroll
+  for (int w = 0; w < kRow; ++w) value(w);
+  T acc = T(0);
+  if (wide) {
+#pragma unroll
+    for (int w = kRow; w < 16; ++w) value(w);
   }
 #pragma unroll
-  for (int w = 0; w < 16; ++w) xv[w] = w < L.W ? L.x[col[w]] : T(0);
-  T acc = T(0);
+  for (int w = 0; w < kRow; ++w) acc += val[w] * xv[w];
+  if (wide) {
 #pragma unroll
-  for (int w = 0; w < 16; ++w) acc += val[w] * xv[w];
+    for (int w = kRow; w < 16; ++w) acc += val[w] * xv[w];
+  }
   return acc;
 }
 
@@ -643,7 +737,7 @@ __global__ __launch_bounds__(256) void k_g_smooth(GStepArgs<T> a) {
   const int i = a.lo + blockIdx.x * 256 + threadIdx.x;
   if (i >= a.hi) return;
   const GLevel<T>& L = a.lev[a.g];
-  L.x[i] = (L.b[i] - g_row(L, i)) / L.diag[i];
+  L.x[i] = (L.b[i] - g_row(L, i, i >= a.wide)) / L.diag[i];
 }
 
 // Residual of level g (one lane per node), kept in r for the restriction.
@@ -652,7 +746,9 @@ __global__ __launch_bounds__(256) void k_g_resid(GStepArgs<T> a) {
   const GLevel<T>& F = a.lev[a.g];
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= F.n) return;
-  F.r[i] = F.b[i] - F.diag[i] * F.x[i] - g_row(F, i);
+  int c = 0;  // the node's colour
+  while (c + 1 < F.ncol && i >= F.color_off[c + 1]) ++c;
+  F.r[i] = F.b[i] - F.diag[i] * F.x[i] - g_row(F, i, i >= F.wide_off[c]);
 }
 
 // Residual of level g restricted to level g+1 (volume weights, every child load issued before
@@ -776,18 +872,22 @@ hipError_t launch_coarse(const CoarseArgs<T>& a, hipStream_t s) {
   hipLaunchKernelGGL((k_coarse<T>), dim3(1), dim3(1024), 0, s, a);
   return hipGetLastError();
 }
-template <typename T>
-hipError_t launch_coarse_mg(const CoarseMGArgs<T>& a, hipStream_t s) {
+template <typename T, bool WIDE>
+static hipError_t launch_graph(const CoarseMGArgs<T>& a, hipStream_t s) {
   static bool attr = false;
   if (!attr) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_coarse_mg<T>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_coarse_mg<T, WIDE>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kGraphLdsTotal);
     if (e != hipSuccess) return e;
     attr = true;
   }
   const int grid = a.xu_n > 0 ? 1 + (a.xu_wgs > 1 ? a.xu_wgs : 1) : 1;
-  hipLaunchKernelGGL((k_coarse_mg<T>), dim3(grid), dim3(1024), a.lds_bytes, s, a);
+  hipLaunchKernelGGL((k_coarse_mg<T, WIDE>), dim3(grid), dim3(1024), a.lds_bytes, s, a);
   return hipGetLastError();
+}
+template <typename T>
+hipError_t launch_coarse_mg(const CoarseMGArgs<T>& a, hipStream_t s) {
+  return a.wide ? launch_graph<T, true>(a, s) : launch_graph<T, false>(a, s);
 }
 template hipError_t launch_coarse_mg<float>(const CoarseMGArgs<float>&, hipStream_t);
 template hipError_t launch_coarse_mg<double>(const CoarseMGArgs<double>&, hipStream_t);

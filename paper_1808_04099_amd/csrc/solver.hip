@@ -230,12 +230,13 @@ template <typename T>
 int coarse_split(bcm_plan* P, const T* b_in, T* x_out, T* xf_out, hipStream_t s) {
   const auto& Ls = P->M->coarse.levels;
   const int S = P->g_split, pre = 2, post = 2;
-  GStepArgs<T> ga{P->at<const GLevel<T>>(P->o_glev), 0, 0, 0, b_in, x_out, xf_out,
+  GStepArgs<T> ga{P->at<const GLevel<T>>(P->o_glev), 0, 0, 0, 0, b_in, x_out, xf_out,
                   P->at<const int32_t>(P->o_perm0), P->nc};
-  auto step = [&](int kind, int g, int n, int lo = 0, int hi = 0) -> int {
+  auto step = [&](int kind, int g, int n, int lo = 0, int hi = 0, int wide = 0) -> int {
     ga.g = g;
     ga.lo = lo;
     ga.hi = hi;
+    ga.wide = wide;
     HIPCHK(timed(P, cls_of(P, "coarse", 0), s, [&] { return launch_g_step<T>(kind, n, ga, s); }),
            "graph multigrid step");
     return BCM_OK;
@@ -245,7 +246,7 @@ int coarse_split(bcm_plan* P, const T* b_in, T* x_out, T* xf_out, hipStream_t s)
     const int nc = int(co.size()) - 1;
     for (int k = 0; k < nc; ++k) {
       const int c = forward ? k : nc - 1 - k;
-      if (int e = step(G_SMOOTH, g, co[c + 1] - co[c], co[c], co[c + 1])) return e;
+      if (int e = step(G_SMOOTH, g, co[c + 1] - co[c], co[c], co[c + 1], Ls[g].wide_off[c])) return e;
     }
     return BCM_OK;
   };
@@ -258,7 +259,7 @@ int coarse_split(bcm_plan* P, const T* b_in, T* x_out, T* xf_out, hipStream_t s)
     }
     if (st) break;
     CoarseMGArgs<T> a{b_in, x_out, xf_out, P->at<const GLevel<T>>(P->o_glev),
-                      P->at<const int32_t>(P->o_perm0), int(P->g_off.size()), S, 1, pre, post,
+                      P->at<const int32_t>(P->o_perm0), int(P->g_off.size()), S, P->M->coarse.wide > S, 1, pre, post,
                       std::max(P->o.coarse_iters, 64), P->at<double>(P->o_gw),
                       P->M->coarse.bottom_inv.empty() ? nullptr : P->at<const T>(P->o_ginv), P->g_lds,
                       P->g_lds_inv};
@@ -353,7 +354,7 @@ int vcycle(bcm_plan* P, const T* q_dot, hipStream_t s, Hook&& before_coarse, con
     if (int st = coarse_split<T>(P, B(L - 1), X(L - 1), F(1, L - 1), s)) return st;
   } else if (P->graph) {
     CoarseMGArgs<T> ga{B(L - 1), X(L - 1), F(1, L - 1), P->at<const GLevel<T>>(P->o_glev),
-                       P->at<const int32_t>(P->o_perm0), int(P->g_off.size()), 0, o.coarse_cycles,
+                       P->at<const int32_t>(P->o_perm0), int(P->g_off.size()), 0, P->M->coarse.wide > 0, o.coarse_cycles,
                        2, 2, std::max(o.coarse_iters, 64),  // the last graph level has <= 64 nodes
                        P->at<double>(P->o_gw),
                        P->M->coarse.bottom_inv.empty() ? nullptr : P->at<const T>(P->o_ginv), P->g_lds,
@@ -1260,6 +1261,7 @@ int upload_graph(bcm_plan* P, hipStream_t s) {
     d.W = L.W;
     d.CW = L.CW;
     for (int c = 0; c <= d.ncol; ++c) d.color_off[c] = L.color_off[c];
+    for (int c = 0; c < d.ncol; ++c) d.wide_off[c] = L.wide_off[c];
     d.lds_x = o.lds_x;
     d.lds_b = o.lds_b;
     d.lds_r = o.lds_r;
