@@ -363,7 +363,8 @@ template <typename TF> hipError_t launch_kinetic(const KineticArgs<TF>& a, int g
 template <typename TF> hipError_t launch_ib_force(const IbArgs<TF>& a, hipStream_t s);
 hipError_t launch_zero_u32(unsigned int* p, hipStream_t s);
 template <typename TF> hipError_t launch_mom(int NL, int mode, const MomArgs<TF>& a, int grid, hipStream_t s);
-template <typename T> hipError_t launch_coarse_mg(const CoarseMGArgs<T>& a, hipStream_t s);
+// fin.n > 0: one more workgroup does that reduction
+template <typename T> hipError_t launch_coarse_mg(const CoarseMGArgs<T>& a, const FinalizeArgs& fin, hipStream_t s);
 // Multi-workgroup steps on one large graph level; n = lanes (cubes, nodes of the range, nodes
 // of the level for G_RESID, or nodes of the coarser level for G_RESTRICT).
 enum { G_GATHER = 0, G_SMOOTH = 1, G_RESTRICT = 2, G_PROLONG = 3, G_SCATTER = 4, G_RESID = 5 };

@@ -71,8 +71,7 @@ __global__ __launch_bounds__(256) void k_export(ExportArgs<T, TO> a) {
 }
 
 // Sum of per-workgroup partials in a fixed order, then the scalar recurrences.
-__global__ __launch_bounds__(1024) void k_finalize(FinalizeArgs a) {
-  __shared__ double red[16];
+__device__ __forceinline__ void finalize_sums(const FinalizeArgs& a, double* red) {
   double s0 = 0.0, s1 = 0.0;
   for (int e = threadIdx.x; e < a.n; e += 1024) {
     s0 += a.p0[e];
@@ -127,6 +126,10 @@ __global__ __launch_bounds__(1024) void k_finalize(FinalizeArgs a) {
     __threadfence_system();
     __hip_atomic_store(&a.mirror->seq, a.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
+}
+__global__ __launch_bounds__(1024) void k_finalize(FinalizeArgs a) {
+  __shared__ double red[16];
+  finalize_sums(a, red);
 }
 
 // Conjugate gradients on the one-cell-per-cube level (the cube graph), one workgroup.
@@ -529,13 +532,13 @@ __device__ __forceinline__ void g_prolong(const GLevel<T>& F, T* x, const T* xc)
 // The vector update x += alpha p of the workgroups after the first of k_coarse_mg: 16-byte
 // non-temporal accesses, the same arithmetic as k_update.
 template <typename T>
-__device__ __forceinline__ void coarse_side_update(const CoarseMGArgs<T>& a) {
+__device__ __forceinline__ void coarse_side_update(const CoarseMGArgs<T>& a, int wgs) {
   typedef T V __attribute__((ext_vector_type(16 / sizeof(T))));
   constexpr int W = 16 / sizeof(T);
   const T al = T(*a.xu_alpha);
   const size_t nv = a.xu_n / W;
   const size_t first = size_t(blockIdx.x - 1) * blockDim.x + threadIdx.x;
-  const size_t stride = size_t(gridDim.x - 1) * blockDim.x;
+  const size_t stride = size_t(wgs) * blockDim.x;
   V* xv = reinterpret_cast<V*>(a.xu_x);
   const V* pv = reinterpret_cast<const V*>(a.xu_p);
   for (size_t e = first; e < nv; e += stride) {
@@ -550,13 +553,18 @@ __device__ __forceinline__ void coarse_side_update(const CoarseMGArgs<T>& a) {
 // WIDE: some level has wide rows (2:1 interfaces).  A kernel of its own, without the rows in
 // registers, which the wide passes would make spill.
 template <typename T, bool WIDE>
-__global__ __launch_bounds__(1024) void k_coarse_mg(CoarseMGArgs<T> a) {
+__global__ __launch_bounds__(1024) void k_coarse_mg(CoarseMGArgs<T> a, FinalizeArgs fin) {
+  __shared__ double red[16];
+  const int with_fin = fin.n > 0 ? 1 : 0;
+  if (with_fin && blockIdx.x == gridDim.x - 1) {  // a reduction that something else waits for
+    finalize_sums(fin, red);
+    return;
+  }
   if (blockIdx.x > 0) {  // the side update (only launched with xu_n > 0)
-    coarse_side_update(a);
+    coarse_side_update(a, int(gridDim.x) - 1 - with_fin);
     return;
   }
   extern __shared__ __align__(16) unsigned char gsm[];
-  __shared__ double red[16];
   __shared__ GLevel<T> lv[kMaxGraphLevels];
   if (threadIdx.x < a.nlev) {
     GLevel<T> L = a.lev[threadIdx.x];
@@ -873,7 +881,7 @@ hipError_t launch_coarse(const CoarseArgs<T>& a, hipStream_t s) {
   return hipGetLastError();
 }
 template <typename T, bool WIDE>
-static hipError_t launch_graph(const CoarseMGArgs<T>& a, hipStream_t s) {
+static hipError_t launch_graph(const CoarseMGArgs<T>& a, const FinalizeArgs& fin, hipStream_t s) {
   static bool attr = false;
   if (!attr) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_coarse_mg<T, WIDE>),
@@ -881,16 +889,16 @@ static hipError_t launch_graph(const CoarseMGArgs<T>& a, hipStream_t s) {
     if (e != hipSuccess) return e;
     attr = true;
   }
-  const int grid = a.xu_n > 0 ? 1 + (a.xu_wgs > 1 ? a.xu_wgs : 1) : 1;
-  hipLaunchKernelGGL((k_coarse_mg<T, WIDE>), dim3(grid), dim3(1024), a.lds_bytes, s, a);
+  const int grid = 1 + (a.xu_n > 0 ? (a.xu_wgs > 1 ? a.xu_wgs : 1) : 0) + (fin.n > 0 ? 1 : 0);
+  hipLaunchKernelGGL((k_coarse_mg<T, WIDE>), dim3(grid), dim3(1024), a.lds_bytes, s, a, fin);
   return hipGetLastError();
 }
 template <typename T>
-hipError_t launch_coarse_mg(const CoarseMGArgs<T>& a, hipStream_t s) {
-  return a.wide ? launch_graph<T, true>(a, s) : launch_graph<T, false>(a, s);
+hipError_t launch_coarse_mg(const CoarseMGArgs<T>& a, const FinalizeArgs& fin, hipStream_t s) {
+  return a.wide ? launch_graph<T, true>(a, fin, s) : launch_graph<T, false>(a, fin, s);
 }
-template hipError_t launch_coarse_mg<float>(const CoarseMGArgs<float>&, hipStream_t);
-template hipError_t launch_coarse_mg<double>(const CoarseMGArgs<double>&, hipStream_t);
+template hipError_t launch_coarse_mg<float>(const CoarseMGArgs<float>&, const FinalizeArgs&, hipStream_t);
+template hipError_t launch_coarse_mg<double>(const CoarseMGArgs<double>&, const FinalizeArgs&, hipStream_t);
 
 template <typename T>
 hipError_t launch_g_step(int kind, int n, const GStepArgs<T>& a, hipStream_t s) {

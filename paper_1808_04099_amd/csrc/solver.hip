@@ -206,15 +206,22 @@ int read_scalars(bcm_plan* P, Scalars* host, hipStream_t s) {
   return BCM_OK;
 }
 
-int finalize(bcm_plan* P, int op, int which0, int which1, int nparts, int first, hipStream_t s) {
+FinalizeArgs finalize_args(bcm_plan* P, int op, int which0, int which1, int nparts, int first) {
   // the two recurrences in the middle of a Krylov iteration are never read by the host before
   // the next finalize: they skip the copy to the pinned mirror and its system-scope fence
   const bool publish = P->mirror && op != OP_ZRZQ && op != OP_PQ;
-  FinalizeArgs a{P->at<double>(P->o_part[which0]), which1 >= 0 ? P->at<double>(P->o_part[which1]) : nullptr,
-                 nparts, P->at<Scalars>(P->o_sc), op, first, publish ? P->mirror : nullptr,
-                 publish ? ++P->mirror_seq : 0u};
+  return FinalizeArgs{P->at<double>(P->o_part[which0]), which1 >= 0 ? P->at<double>(P->o_part[which1]) : nullptr,
+                      nparts, P->at<Scalars>(P->o_sc), op, first, publish ? P->mirror : nullptr,
+                      publish ? ++P->mirror_seq : 0u};
+}
+
+int finalize(bcm_plan* P, const FinalizeArgs& a, hipStream_t s) {
   HIPCHK(timed(P, cls_of(P, "finalize", 0), s, [&] { return launch_finalize(a, s); }), "k_finalize");
   return BCM_OK;
+}
+
+int finalize(bcm_plan* P, int op, int which0, int which1, int nparts, int first, hipStream_t s) {
+  return finalize(P, finalize_args(P, op, which0, which1, nparts, first), s);
 }
 
 // Export the faces of an FP64 field (kc_ir without an update).
@@ -263,7 +270,8 @@ int coarse_split(bcm_plan* P, const T* b_in, T* x_out, T* xf_out, hipStream_t s)
                       std::max(P->o.coarse_iters, 64), P->at<double>(P->o_gw),
                       P->M->coarse.bottom_inv.empty() ? nullptr : P->at<const T>(P->o_ginv), P->g_lds,
                       P->g_lds_inv};
-    HIPCHK(timed(P, cls_of(P, "coarse", 0), s, [&] { return launch_coarse_mg<T>(a, s); }), "k_coarse_mg");
+    HIPCHK(timed(P, cls_of(P, "coarse", 0), s, [&] { return launch_coarse_mg<T>(a, FinalizeArgs{}, s); }),
+           "k_coarse_mg");
     for (int g = S - 1; g >= 0 && !st; --g) {
       st = step(G_PROLONG, g, Ls[g].n);
       for (int k = 0; k < post && !st; ++k) st = sweep(g, false);
@@ -350,7 +358,7 @@ int vcycle(bcm_plan* P, const T* q_dot, hipStream_t s, Hook&& before_coarse, con
     }
   }
   if (P->graph && P->g_split > 0) {
-    if (const int st = before_coarse(nullptr)) return st;
+    if (const int st = before_coarse(nullptr, nullptr)) return st;
     if (int st = coarse_split<T>(P, B(L - 1), X(L - 1), F(1, L - 1), s)) return st;
   } else if (P->graph) {
     CoarseMGArgs<T> ga{B(L - 1), X(L - 1), F(1, L - 1), P->at<const GLevel<T>>(P->o_glev),
@@ -359,10 +367,11 @@ int vcycle(bcm_plan* P, const T* q_dot, hipStream_t s, Hook&& before_coarse, con
                        P->at<double>(P->o_gw),
                        P->M->coarse.bottom_inv.empty() ? nullptr : P->at<const T>(P->o_ginv), P->g_lds,
                       P->g_lds_inv};
-    if (const int st = before_coarse(&ga)) return st;  // may hand it a vector update to carry
-    HIPCHK(timed(P, cls_of(P, "coarse", 0), s, [&] { return launch_coarse_mg<T>(ga, s); }), "k_coarse_mg");
+    FinalizeArgs fin{};
+    if (const int st = before_coarse(&ga, &fin)) return st;  // may hand it an update and a reduction
+    HIPCHK(timed(P, cls_of(P, "coarse", 0), s, [&] { return launch_coarse_mg<T>(ga, fin, s); }), "k_coarse_mg");
   } else {
-    if (const int st = before_coarse(nullptr)) return st;
+    if (const int st = before_coarse(nullptr, nullptr)) return st;
     CoarseArgs<T> ca{P->at<const CubeMeta>(P->o_meta), P->nc, double(P->n), B(L - 1), X(L - 1),
                      F(1, L - 1), P->at<double>(P->o_cw), o.coarse_iters};
     HIPCHK(timed(P, cls_of(P, "coarse", 0), s, [&] { return launch_coarse<T>(ca, s); }), "k_coarse");
@@ -510,7 +519,10 @@ int krylov(bcm_plan* P, T* x, bool x_zero, double thr, int max_iter, double hist
   // lack of two, by a norm that one iteration would have to cut a hundredfold) is read after
   // the launches of the V-cycle (unread): if it does end the solve, that V-cycle was for nothing.
   // 64 cubes of 16^3 in FP64: 1233 -> 1198 us a projection.
+  // The reduction behind an unread check (rr_fin) rides with the launch of the coarse solve:
+  // 64 cubes of 16^3 1101 -> 1071 us a projection.
   bool unread = false;
+  FinalizeArgs rr_fin{};
   auto far = [&]() {
     return P->mirror && rr_b > 0.0 && (rr_a > 0.0 ? rr_b * (rr_b / rr_a) > 30.0 * thr : 1e-4 * rr_b > thr);
   };
@@ -538,11 +550,16 @@ int krylov(bcm_plan* P, T* x, bool x_zero, double thr, int max_iter, double hist
   };
   auto check = [&](int it, int nrr, bool may_defer, bool& stop) -> int {
     stop = false;
-    if (const int st = finalize(P, OP_RR, 0, -1, nrr, 0, s)) return st;
+    const FinalizeArgs f = finalize_args(P, OP_RR, 0, -1, nrr, 0);
+    const bool checked = (it + 1) % P->o.check_every == 0 || it + 1 >= max_iter;
+    unread = checked && may_defer && far();
     log.iters++;
-    if ((it + 1) % P->o.check_every != 0 && it + 1 < max_iter) return BCM_OK;
-    unread = may_defer && far();
-    return unread ? BCM_OK : read_check(stop);
+    if (unread) {
+      rr_fin = f;
+      return BCM_OK;
+    }
+    if (const int st = finalize(P, f, s)) return st;
+    return checked ? read_check(stop) : BCM_OK;
   };
   // the pending r update on its own (probe: only its <r, r>), with per-cube partials
   auto update_alone = [&](int it, bool probe, bool& stop) -> int {
@@ -570,7 +587,15 @@ int krylov(bcm_plan* P, T* x, bool x_zero, double thr, int max_iter, double hist
     }
     const bool first = !fcg || (it == 0 && !(flex && carry));  // no direction to orthogonalise against
     int st = vcycle<T>(P, (flex && !first) ? q : nullptr, s,
-                       [&](CoarseMGArgs<T>* carrier) { return start_x(true, carrier); },
+                       [&](CoarseMGArgs<T>* carrier, FinalizeArgs* fin) -> int {
+                         if (rr_fin.n > 0) {
+                           const FinalizeArgs f = rr_fin;
+                           rr_fin.n = 0;
+                           if (fin) *fin = f;
+                           else if (const int e = finalize(P, f, s)) return e;
+                         }
+                         return start_x(true, carrier);
+                       },
                        r_pending ? &ur : nullptr, n_pq,
                        [&](bool& stop_) -> int {
                          n_pq = 0;  // (the pre-smoother has formed alpha)
