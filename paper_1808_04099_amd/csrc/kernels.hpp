@@ -309,6 +309,16 @@ struct IbArgs {
   unsigned int* errors;   // particles skipped (outside the mesh, or support leaving one level)
 };
 
+struct IbCopyArgs {         // three fields of n16 x 16 bytes, 16-byte aligned; errors = 0
+  const void* src[3];
+  void* dst[3];
+  size_t n16;
+  unsigned int* errors;
+};
+constexpr size_t kIbCopyGrid = 8192;  // workgroups a field at most
+hipError_t launch_ib_copy(const IbCopyArgs& a, hipStream_t s);
+hipError_t launch_ib_publish(const unsigned int* errors, ScalarMirror* mirror, uint32_t seq, hipStream_t s);
+
 // Wavelet compression of an FP64 cell field (kernels_codec.hip).
 struct CodecArgs {
   int n_cubes, n, levels;

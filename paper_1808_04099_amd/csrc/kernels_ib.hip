@@ -13,6 +13,8 @@
 // or whose support would leave that level's cubes or the domain, is skipped and counted.
 // Spreading adds with atomics: contributions of particles that share a cell are summed in
 // whatever order the lanes reach them (reproducible to rounding, not bit for bit).
+#include <algorithm>
+
 #include "kernels.hpp"
 
 namespace bcm {
@@ -135,7 +137,46 @@ __global__ __launch_bounds__(256) void k_ib_force(IbArgs<TF> a) {
 
 __global__ void k_zero_u32(unsigned int* p) { *p = 0u; }
 
+// u* = u~ for the three components in one launch, 16 bytes a lane, four loads in flight, past the
+// caches (each value is touched once), and the skip counter to zero.  Bound by memory: 3 x 33.5M
+// FP64 values in 269 us, 6.0 TB/s (three device-to-device copies: about 310 us; the whole call,
+// with the counter read through the pinned mirror instead of a copy and a stream
+// synchronisation, 377 -> 320 us; 512 or 2048 workgroups a field: 337 and 328 us).
+__global__ __launch_bounds__(256) void k_ib_copy(IbCopyArgs a) {
+  typedef unsigned int V __attribute__((ext_vector_type(4)));
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *a.errors = 0u;
+  const V* src = static_cast<const V*>(a.src[blockIdx.y]);
+  V* dst = static_cast<V*>(a.dst[blockIdx.y]);
+  const size_t step = (size_t)gridDim.x * 1024;
+  for (size_t e = (size_t)blockIdx.x * 1024 + threadIdx.x; e < a.n16; e += step) {
+    V v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (e + 256 * q < a.n16) v[q] = __builtin_nontemporal_load(src + e + 256 * q);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (e + 256 * q < a.n16) __builtin_nontemporal_store(v[q], dst + e + 256 * q);
+  }
+}
+
+// The skip counter for the host, after every particle (the last launch of a call).
+__global__ void k_ib_publish(const unsigned int* errors, ScalarMirror* mirror, uint32_t seq) {
+  mirror->sc.spare[0] = double(*errors);
+  __threadfence_system();
+  __hip_atomic_store(&mirror->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 }  // namespace
+
+hipError_t launch_ib_copy(const IbCopyArgs& a, hipStream_t s) {
+  const size_t wgs = (a.n16 + 1023) / 1024;
+  hipLaunchKernelGGL(k_ib_copy, dim3((unsigned)std::min<size_t>(wgs, kIbCopyGrid), 3), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+hipError_t launch_ib_publish(const unsigned int* errors, ScalarMirror* mirror, uint32_t seq, hipStream_t s) {
+  hipLaunchKernelGGL(k_ib_publish, dim3(1), dim3(1), 0, s, errors, mirror, seq);
+  return hipGetLastError();
+}
 
 template <typename TF>
 hipError_t launch_ib_force(const IbArgs<TF>& a, hipStream_t s) {

@@ -1119,7 +1119,6 @@ int ib_force_impl(bcm_plan* P, const bcm_particles* pt, const void* const u_tild
     a.usc[d] = pt->us_const[d];
     a.u[d] = static_cast<const TF*>(u_tilde[d]);
     a.ustar[d] = static_cast<TF*>(u_star[d]);
-    HIPCHK(hipMemcpyAsync(u_star[d], u_tilde[d], P->cells * sizeof(TF), hipMemcpyDeviceToDevice, s), "copy u~");
   }
   a.n_particles = pt->n;
   a.X = pt->X;
@@ -1130,11 +1129,44 @@ int ib_force_impl(bcm_plan* P, const bcm_particles* pt, const void* const u_tild
   a.Up = Up;
   a.Fp = Fp;
   a.errors = P->at<unsigned int>(P->o_iberr);
-  HIPCHK(launch_zero_u32(a.errors, s), "zero the skip counter");
+  // u* = u~ by one kernel where it can move 16 bytes at a time and no output overlaps another
+  // field (the copies in turn have an order, its do not)
+  const size_t bytes = P->cells * sizeof(TF);
+  IbCopyArgs c{};
+  uintptr_t low = bytes;
+  bool apart = true;
+  for (int d = 0; d < 3; ++d) {
+    c.src[d] = u_tilde[d];
+    c.dst[d] = u_star[d];
+    low |= reinterpret_cast<uintptr_t>(u_tilde[d]) | reinterpret_cast<uintptr_t>(u_star[d]);
+    for (int q = 0; q < 3; ++q) {
+      auto overlap = [&](const void* x, const void* y) {
+        const uintptr_t i = reinterpret_cast<uintptr_t>(x), j = reinterpret_cast<uintptr_t>(y);
+        return (i > j ? i - j : j - i) < bytes;
+      };
+      apart = apart && !overlap(u_star[d], u_tilde[q]) && (q == d || !overlap(u_star[d], u_star[q]));
+    }
+  }
+  c.n16 = bytes / 16;
+  c.errors = a.errors;
+  if (apart && low % 16 == 0) {
+    HIPCHK(launch_ib_copy(c, s), "k_ib_copy");
+  } else {
+    for (int d = 0; d < 3; ++d)
+      HIPCHK(hipMemcpyAsync(u_star[d], u_tilde[d], bytes, hipMemcpyDeviceToDevice, s), "copy u~");
+    HIPCHK(launch_zero_u32(a.errors, s), "zero the skip counter");
+  }
   HIPCHK(timed(P, cls_of(P, "ib", 0), s, [&] { return launch_ib_force<TF>(a, s); }), "k_ib_force");
   unsigned int skipped = 0;
-  HIPCHK(hipMemcpyAsync(&skipped, a.errors, sizeof(skipped), hipMemcpyDeviceToHost, s), "skip counter readback");
-  HIPCHK(hipStreamSynchronize(s), "stream synchronize");
+  if (P->mirror) {
+    HIPCHK(launch_ib_publish(a.errors, P->mirror, ++P->mirror_seq, s), "k_ib_publish");
+    Scalars sc;
+    if (const int e = read_scalars(P, &sc, s)) return e;
+    skipped = unsigned(sc.spare[0]);
+  } else {
+    HIPCHK(hipMemcpyAsync(&skipped, a.errors, sizeof(skipped), hipMemcpyDeviceToHost, s), "skip counter readback");
+    HIPCHK(hipStreamSynchronize(s), "stream synchronize");
+  }
   if (skipped) {
     set_error("bcm_ib_force: " + std::to_string(skipped) +
               " particles skipped (outside the mesh, or their 3x3x3 support leaves their cube's level"
