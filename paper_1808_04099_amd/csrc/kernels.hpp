@@ -247,6 +247,7 @@ struct KineticArgs {    // sum_i V_i |u_i|^2 (partials per workgroup); g_u = gsc
   TF* gu[3];            // nullptr: no seed
   double gscale;
   double* part;         // nullptr: no sum
+  int apart;           // no output overlaps a field (but for its own component in place)
 };
 
 // Momentum sub-step (kernels_mom.hip).  Face buffers: 4 n^2 values per cube and component.

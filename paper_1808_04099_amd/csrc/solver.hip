@@ -969,6 +969,20 @@ int adjoint_impl(bcm_plan* P, const bcm_adjoint_in* in, bcm_adjoint_out* out, bc
 }
 
 // J = (rho/2) sum_i V_i |u_i|^2 and the seed cotangent g_scale rho V_i u_i.
+// No output overlaps another output or an input, but for the same component in place.
+template <typename TF>
+int kinetic_apart(const KineticArgs<TF>& a, size_t bytes) {
+  auto overlap = [&](const void* x, const void* y) {
+    const uintptr_t i = reinterpret_cast<uintptr_t>(x), j = reinterpret_cast<uintptr_t>(y);
+    return (i > j ? i - j : j - i) < bytes;
+  };
+  for (int i = 0; a.gu[0] && i < 3; ++i)
+    for (int j = 0; j < 3; ++j)
+      if ((overlap(a.gu[i], a.u[j]) && !(i == j && a.gu[i] == a.u[j])) || (i != j && overlap(a.gu[i], a.gu[j])))
+        return 0;
+  return 1;
+}
+
 template <typename TF>
 int kinetic_impl(bcm_plan* P, const void* const u[3], double rho, double g_scale, double* J,
                  void* const g_u[3], hipStream_t s) {
@@ -981,6 +995,7 @@ int kinetic_impl(bcm_plan* P, const void* const u[3], double rho, double g_scale
     ka.gu[d] = g_u ? static_cast<TF*>(g_u[d]) : nullptr;
   }
   ka.gscale = g_scale * rho;
+  ka.apart = kinetic_apart(ka, P->cells * sizeof(TF));
   const int grid = std::min(P->nc, 2048);  // the partial buffers hold >= n_cubes values
   ka.part = J ? P->at<double>(P->o_part[0]) : nullptr;
   HIPCHK(launch_kinetic<TF>(ka, grid, s), "k_kinetic");
@@ -1261,6 +1276,7 @@ int kinetic_noalloc_impl(bcm_plan* P, const void* const u[3], double rho, double
     ka.gu[d] = g_u ? static_cast<TF*>(g_u[d]) : nullptr;
   }
   ka.gscale = g_scale * rho;
+  ka.apart = kinetic_apart(ka, P->cells * sizeof(TF));
   const int grid = std::min(P->nc, 2048);  // the same grid as bcm_kinetic_energy
   if (grid > kNoAllocParts) {
     set_error("bcm_kinetic_energy_noalloc: more partial sums than the scratch array holds");
