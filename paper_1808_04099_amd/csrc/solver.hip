@@ -1302,30 +1302,32 @@ int kinetic_noalloc_impl(bcm_plan* P, const void* const u[3], double rho, double
 template <typename T>
 int upload_graph(bcm_plan* P, hipStream_t s) {
   const auto& Ls = P->M->coarse.levels;
-  std::vector<std::vector<T>> keep;
   std::vector<GLevel<T>> lev(Ls.size());
-  auto put = [&](size_t off, const void* src, size_t bytes) -> hipError_t {
-    if (bytes == 0) return hipSuccess;
-    return hipMemcpyAsync(P->ws + off, src, bytes, hipMemcpyHostToDevice, s);
+  // everything goes into an image of the graph's part of the workspace (its last part) and up in
+  // one copy: some ten small copies a level at several microseconds each were most of a bind
+  // (planning and binding 16 x 8 x 8 cubes 364 -> 298 us, 21 x 13 x 11 cubes 373 -> 252 us)
+  const size_t base = P->g_off[0].col;
+  std::vector<char> image(P->ws_bytes - base, 0);
+  auto put = [&](size_t off, const void* src, size_t bytes) {
+    if (bytes) std::memcpy(image.data() + (off - base), src, bytes);
   };
-  auto conv = [&](const std::vector<double>& v) -> const std::vector<T>& {
-    keep.emplace_back(v.begin(), v.end());
-    return keep.back();
+  auto put_as = [&](size_t off, const std::vector<double>& v) {
+    T* d = reinterpret_cast<T*>(image.data() + (off - base));
+    for (size_t e = 0; e < v.size(); ++e) d[e] = T(v[e]);
   };
-  keep.reserve(4 * Ls.size() + 1);
   for (size_t g = 0; g < Ls.size(); ++g) {
     const CoarseLevel& L = Ls[g];
     const bcm_plan::GOff& o = P->g_off[g];
-    HIPCHK(put(o.col, L.e_col.data(), L.e_col.size() * 4), "upload graph columns");
-    HIPCHK(put(o.val, conv(L.e_val).data(), L.e_val.size() * sizeof(T)), "upload graph values");
-    HIPCHK(put(o.diag, conv(L.e_diag).data(), L.e_diag.size() * sizeof(T)), "upload graph diagonal");
-    HIPCHK(put(o.vol, conv(L.e_vol).data(), L.e_vol.size() * sizeof(T)), "upload graph volumes");
-    HIPCHK(put(o.parent, L.e_parent.data(), L.e_parent.size() * 4), "upload graph parents");
+    put(o.col, L.e_col.data(), L.e_col.size() * 4);
+    put_as(o.val, L.e_val);
+    put_as(o.diag, L.e_diag);
+    put_as(o.vol, L.e_vol);
+    put(o.parent, L.e_parent.data(), L.e_parent.size() * 4);
     if (!L.e_pcol.empty())
-      HIPCHK(put(o.pcol, L.e_pcol.data(), L.e_pcol.size() * 4), "upload packed graph columns");
+      put(o.pcol, L.e_pcol.data(), L.e_pcol.size() * 4);
     if (g > 0) {
-      HIPCHK(put(o.child, L.e_child.data(), L.e_child.size() * 4), "upload graph children");
-      HIPCHK(put(o.child_w, conv(L.e_child_w).data(), L.e_child_w.size() * sizeof(T)), "upload graph weights");
+      put(o.child, L.e_child.data(), L.e_child.size() * 4);
+      put_as(o.child_w, L.e_child_w);
     }
     GLevel<T>& d = lev[g];
     std::memset(&d, 0, sizeof(d));
@@ -1351,10 +1353,10 @@ int upload_graph(bcm_plan* P, hipStream_t s) {
     d.pcol = L.e_pcol.empty() ? nullptr : P->at<const uint32_t>(o.pcol);
     d.uval = T(L.uval);
   }
-  HIPCHK(put(P->o_perm0, Ls[0].perm.data(), Ls[0].perm.size() * 4), "upload graph permutation");
-  HIPCHK(put(P->o_ginv, conv(P->M->coarse.bottom_inv).data(), P->M->coarse.bottom_inv.size() * sizeof(T)),
-         "upload bottom inverse");
-  HIPCHK(put(P->o_glev, lev.data(), lev.size() * sizeof(GLevel<T>)), "upload graph levels");
+  put(P->o_perm0, Ls[0].perm.data(), Ls[0].perm.size() * 4);
+  put_as(P->o_ginv, P->M->coarse.bottom_inv);
+  put(P->o_glev, lev.data(), lev.size() * sizeof(GLevel<T>));
+  HIPCHK(hipMemcpyAsync(P->ws + base, image.data(), image.size(), hipMemcpyHostToDevice, s), "upload cube graph");
   HIPCHK(hipStreamSynchronize(s), "stream synchronize");
   return BCM_OK;
 }
