@@ -195,7 +195,7 @@ __global__ __launch_bounds__(256, 4) void k_wc_encode(CodecArgs a) {
   __shared__ int pre[W::UG + 1];
   __shared__ int bad[W::CPB];
   u32x4_alias* zero4 = reinterpret_cast<u32x4_alias*>(c);
-  unsigned int* words = reinterpret_cast<unsigned int*>(c);  // once the coefficients are in registers
+  u32_alias* words = reinterpret_cast<u32_alias*>(c);  // once the coefficients are in registers
   static_assert(sizeof(c) >= size_t(W::UW) * 4, "the words of a unit fit in the cube's LDS block");
   // (one cube per unit at 16^3: s is then a constant, and the cube and its pointers scalar)
   const int t = threadIdx.x, s = W::CPB == 1 ? 0 : t / W::N2, l = W::CPB == 1 ? t : t % W::N2;
