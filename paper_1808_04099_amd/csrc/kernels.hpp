@@ -184,15 +184,15 @@ struct ForceArgs {      // u* = (1 - alpha) u~ + alpha u_s; export face-normal c
   TF* ustar[3];
   TF* uf;
   uint8_t* body;        // 16^3 only: per cube 1 if forced (some alpha != 0), else u* = u~ and only
-                        // its faces are written; nullptr = every cube forced and stored
+                        // its faces are written
 };
 
 template <typename TF>
 struct DivArgs {        // b = (rho/dt) div(U*)
   Geom g;
   const TF* ustar[3];
-  const TF* u[3];       // u~, read instead of u* in cubes whose body flag is 0
-  const uint8_t* body;  // nullptr: u* everywhere
+  const TF* u[3];       // 16^3: u~, read instead of u* in cubes whose body flag is 0
+  const uint8_t* body;
   const TF* uf;
   double U_in, inv_c;
   double* b;
@@ -204,8 +204,8 @@ struct CorrectArgs {    // u_new = u* - c G_c p; optional face velocities U* - c
   const double* p;
   const double* pf;
   const TF* ustar[3];
-  const TF* u[3];       // u~, read instead of u* in cubes whose body flag is 0 (16^3)
-  const uint8_t* body;  // nullptr: u* everywhere
+  const TF* u[3];       // 16^3: u~, read instead of u* in cubes whose body flag is 0
+  const uint8_t* body;
   const TF* uf;
   double U_in, c;
   TF* unew[3];

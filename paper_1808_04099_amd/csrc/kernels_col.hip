@@ -1281,10 +1281,10 @@ __device__ __forceinline__ T face_get(const T* f, int c, int of, int t1, int t2)
 
 // u* = (1 - alpha) u~ + alpha u_s, and the face-normal component of u* on each face.  A pure
 // stream: planes are processed four at a time so that few values are live per lane.
-// With a.body set, only the cubes with some alpha != 0 (body cubes) are forced and stored; the
-// kernel records the flag per cube, and for the other cubes, where u* = u~, it writes only the
-// face slabs of u~ (u_x is read whole for its x faces, u_y two rows per plane, u_z two planes);
-// the divergence and correction kernels then read u~ for them.
+// Only the cubes with some alpha != 0 (body cubes) are forced and stored; the kernel records the
+// flag per cube, and for the other cubes, where u* = u~, it writes only the face slabs of u~ (u_x
+// is read whole for its x faces, u_y two rows per plane, u_z two planes); the divergence and
+// correction kernels then read u~ for them.
 template <typename TF>
 __global__ __launch_bounds__(256) void k16_force(ForceArgs<TF> a) {
   const int t = threadIdx.x, i = t & 15, j = t >> 4;
@@ -1292,39 +1292,37 @@ __global__ __launch_bounds__(256) void k16_force(ForceArgs<TF> a) {
   for (int w = blockIdx.x; w < n; w += gridDim.x) {
     const int c = ro_load(a.g.launch, w);
     TF* base = a.uf + (size_t)c * Col<16>::F;
-    if (a.body) {
-      // alpha and the face sources of u~ are loaded together, before the decision; all three
-      // comparisons wait only on loads issued before them
-      const size_t g0 = (size_t)c * 4096 + t;
-      const bool ry = j == 0 || j == 15;
-      const TF* ap = a.alpha ? a.alpha : a.u[0];  // no alpha: loads that decide nothing
-      const TF* yp = a.u[1] + (ry ? g0 : (size_t)c * 4096 + (t & 15));  // row j = 0 otherwise
-      TF al[16], ux[16], uy[16], uz[2];
+    // alpha and the face sources of u~ are loaded together, before the decision; all three
+    // comparisons wait only on loads issued before them
+    const size_t g0 = (size_t)c * 4096 + t;
+    const bool ry = j == 0 || j == 15;
+    const TF* ap = a.alpha ? a.alpha : a.u[0];  // no alpha: loads that decide nothing
+    const TF* yp = a.u[1] + (ry ? g0 : (size_t)c * 4096 + (t & 15));  // row j = 0 otherwise
+    TF al[16], ux[16], uy[16], uz[2];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      al[k] = ld_nt(ap + g0 + k * 256);
+      ux[k] = ld_nt(a.u[0] + g0 + k * 256);
+      uy[k] = ld_nt(yp + k * 256);
+    }
+    uz[0] = ld_nt(a.u[2] + g0);
+    uz[1] = ld_nt(a.u[2] + g0 + 15 * 256);
+    bool nz = false;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) nz |= al[k] != TF(0);
+    nz = nz && a.alpha != nullptr;
+    const bool any = __syncthreads_or(nz);
+    if (t == 0) a.body[c] = any ? 1 : 0;
+    if (!any) {
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
-        al[k] = ld_nt(ap + g0 + k * 256);
-        ux[k] = ld_nt(a.u[0] + g0 + k * 256);
-        uy[k] = ld_nt(yp + k * 256);
+        if (i == 0) base[0 * 256 + k * 16 + j] = ux[k];
+        if (i == 15) base[1 * 256 + k * 16 + j] = ux[k];
+        if (ry) base[(j ? 3 : 2) * 256 + k * 16 + i] = uy[k];
       }
-      uz[0] = ld_nt(a.u[2] + g0);
-      uz[1] = ld_nt(a.u[2] + g0 + 15 * 256);
-      bool nz = false;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) nz |= al[k] != TF(0);
-      nz = nz && a.alpha != nullptr;
-      const bool any = __syncthreads_or(nz);
-      if (t == 0) a.body[c] = any ? 1 : 0;
-      if (!any) {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          if (i == 0) base[0 * 256 + k * 16 + j] = ux[k];
-          if (i == 15) base[1 * 256 + k * 16 + j] = ux[k];
-          if (ry) base[(j ? 3 : 2) * 256 + k * 16 + i] = uy[k];
-        }
-        base[4 * 256 + j * 16 + i] = uz[0];
-        base[5 * 256 + j * 16 + i] = uz[1];
-        continue;
-      }
+      base[4 * 256 + j * 16 + i] = uz[0];
+      base[5 * 256 + j * 16 + i] = uz[1];
+      continue;
     }
 #pragma unroll 1
     for (int k0 = 0; k0 < 16; k0 += 4) {
@@ -1332,12 +1330,12 @@ __global__ __launch_bounds__(256) void k16_force(ForceArgs<TF> a) {
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         const size_t g = (size_t)c * 4096 + (k0 + kk) * 256 + t;
-        const TF al = a.alpha ? ld_nt(a.alpha + g) : TF(0);
+        const TF fr = ld_nt(a.alpha + g);  // (some alpha of the cube is not 0)
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
           const TF ut = ld_nt(a.u[d] + g);
           const TF us = a.us[d] ? ld_nt(a.us[d] + g) : TF(a.usc[d]);
-          v[d][kk] = a.alpha ? (TF(1) - al) * ut + al * us : ut;
+          v[d][kk] = (TF(1) - fr) * ut + fr * us;
         }
       }
 #pragma unroll
@@ -1368,7 +1366,7 @@ __global__ __launch_bounds__(256) void k16_div(DivArgs<TF> a) {
     const int c = ro_load(a.g.launch, w);
     MetaRO& m = meta_ro(a.g.meta, c);
     const double ih = 1.0 / m.h;
-    const bool forced = !a.body || ro_byte(a.body, c) != 0;  // u* stored, else u* = u~
+    const bool forced = ro_byte(a.body, c) != 0;  // u* stored, else u* = u~
     const TF* src[3] = {forced ? a.ustar[0] : a.u[0], forced ? a.ustar[1] : a.u[1],
                         forced ? a.ustar[2] : a.u[2]};
     double acc[16];
@@ -1634,7 +1632,7 @@ __global__ __launch_bounds__(256) void k16_correct(CorrectArgs<TF> a) {
     const int cc = (j + 1) * 18 + (i + 1);
     // u* of plane k + 1 is loaded while plane k is computed (the loads would otherwise start
     // only after each plane's barrier)
-    const bool forced = !a.body || ro_byte(a.body, c) != 0;  // u* stored, else u* = u~
+    const bool forced = ro_byte(a.body, c) != 0;  // u* stored, else u* = u~
     const TF* src[3] = {forced ? a.ustar[0] : a.u[0], forced ? a.ustar[1] : a.u[1],
                         forced ? a.ustar[2] : a.u[2]};
     TF us[3], usn[3], below = FACES ? hu[FACES ? 4 : 0] : TF(0);  // u*_z of the plane below

@@ -824,9 +824,9 @@ __global__ __launch_bounds__(256) void k_scale(ScaleArgs a) {
 // ------------------------------------------------------------------------------------------
 // Launchers
 // ------------------------------------------------------------------------------------------
+// (the component faces of 16^3 cubes are written by their forcing kernel)
 #define BCM_DISPATCH_NL(NLV, CALL)                 \
   switch (NLV) {                                   \
-    case 16: { constexpr int NLC = 16; CALL; } break; \
     case 8: { constexpr int NLC = 8; CALL; } break;   \
     case 4: { constexpr int NLC = 4; CALL; } break;   \
     case 2: { constexpr int NLC = 2; CALL; } break;   \
