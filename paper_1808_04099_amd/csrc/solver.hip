@@ -659,10 +659,11 @@ int residual64(bcm_plan* P, const double* p, const double* b, TO* r, double rsca
 
 // The last search direction is carried into the next refinement step while the true <r, r> is at
 // most this many times the recurrence's: the new residual is then the old one but for a little
-// rounding, and still orthogonal to that direction.  Where FP32 rounding made most of the new
-// residual (ten times the recurrence's norm on a rough right-hand side), carrying the direction
-// slowed that solve from 13 to 23 iterations.
-constexpr double kCarryMax = 1.2;
+// rounding, and still orthogonal to that direction.  Where carrying saves an iteration, the ratio
+// was at most 1.02; where FP32 rounding makes up more of the new residual, carrying costs
+// iterations (2048 cubes of 16^3, a rough right-hand side: a ratio of 94 after the first step and
+// 1.11 after the second; 13 iterations without, 24 carrying both times, 15 the second alone).
+constexpr double kCarryMax = 1.05;
 
 constexpr double kFp64Floor = 64 * 2.220446049250313e-16;  // relative residual FP64 can reach
 
