@@ -281,8 +281,10 @@ __device__ __forceinline__ T nbsum_z(const T* tile, const int (&zb)[4], int o, c
 // The partial sums of a previous launch, summed by every workgroup in one fixed order (lane t
 // takes entries t, t + 256, ..., then the wavefronts in order): the launch that needs a
 // recurrence's scalar reduces it itself.  A finalize launch in between costs about 6 us (4.6 us
-// and the gap), this about 1 us at the start of the kernel, while its first loads are in
-// flight: 64 cubes of 16^3 in FP64 1285 -> 1233 us a projection.
+// and the gap), this about 1 us at the start of the kernel on small meshes, while its first loads
+// are in flight (64 cubes of 16^3 in FP64 1130 -> 1080 us a projection), and up to 5 us where the
+// producer's grid is full (8192 cubes: apply 110 -> 115 us a launch, a mixed projection 7.98 ->
+// 7.91 ms).
 struct Parts {
   double s0 = 0.0, s1 = 0.0;
   __device__ void load(const double* p0, const double* p1, int n) {
@@ -1495,8 +1497,9 @@ __global__ __launch_bounds__(256) void k16_adj_gp(AdjGpArgs<TF> a) {
 
 // Transpose of the right-hand side and the forcing (see k_adj_rhs): lambda goes through LDS one
 // plane at a time as p does in k16_correct, and the other fields stream past it, one plane
-// ahead.  104 bytes a cell (112 accumulating): 8.4M cells took 310 us with the whole padded
-// tile of lambda in LDS (three workgroups a CU, nothing loaded ahead), and 222 us here.
+// ahead.  96 bytes a cell in FP64 (104 accumulating, 24 more with body velocity fields): 8.4M
+// cells took 310 us with the whole padded tile of lambda in LDS (three workgroups a CU, nothing
+// loaded ahead), and 222 us here.
 template <typename TF, bool ML>
 __global__ __launch_bounds__(256) void k16_adj_rhs(AdjRhsArgs<TF> a) {
   __shared__ double pl[2][P16];

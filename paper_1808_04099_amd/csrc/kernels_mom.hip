@@ -22,13 +22,13 @@
 // one barrier a plane), where each lane also puts its share of the ring rows.  What plane k + 1
 // needs is loaded before plane k is computed.  Arithmetic is FP64 whatever the field type.
 //
-// What bounds it: HBM.  A Crank-Nicolson sweep of 33.5M cells in FP64 takes 0.76 ms and moves
-// 4.0 GB (96 bytes per cell are 3.2 GB; the rest is halo rows, planes and the face buffers),
-// 5.3 TB/s; the VALU is busy 330 us of it.  With every neighbour through LDS, two barriers a
-// plane and nothing loaded ahead it took 0.99 ms, and a separate export pass 0.2 ms a step.
-// Two waves a SIMD (about 250 registers): three spill 90 registers and take three times as
-// long; reading the y neighbours from memory instead of LDS keeps the L1 path busy 65% of the
-// time (0.98 ms).
+// What bounds it: HBM, with what two waves a SIMD keep in flight.  A Crank-Nicolson sweep of
+// 33.5M cells in FP64 takes 0.81 ms and moves 4.0 GB (96 bytes per cell are 3.2 GB; the rest is
+// halo rows, planes and the face buffers), 4.9 TB/s; the VALU is busy 44% of it.  With every
+// neighbour through LDS, two barriers a plane and nothing loaded ahead it took 1.00 ms, and a
+// separate export pass 0.2 ms a step.  About 250 registers: three waves a SIMD spill 90 of them
+// and take three times as long; reading the y neighbours from memory instead of LDS keeps the L1
+// path busy 65% of the time (0.98 ms).
 #include "kernels.hpp"
 #include "tile.hpp"
 

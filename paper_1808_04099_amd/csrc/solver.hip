@@ -518,7 +518,10 @@ int krylov(bcm_plan* P, T* x, bool x_zero, double thr, int max_iter, double hist
   // next launch, about 10 us.  One that cannot end the solve by what the last two say (or, for
   // lack of two, by a norm that one iteration would have to cut a hundredfold) is read after
   // the launches of the V-cycle (unread): if it does end the solve, that V-cycle was for nothing.
-  // 64 cubes of 16^3 in FP64: 1233 -> 1198 us a projection.
+  // Read late against read at once: 64 cubes of 16^3 in FP64 1080 against 1155 us a projection, 512
+  // in mixed precision 1470 against 1525 us, 8192 7.91 against 7.97 ms.  The limits below are not
+  // critical: 3 and 1e-2 instead of 30 and 1e-4 gain up to 1%, for more V-cycles that may be for
+  // nothing; 1000 and 1e-6 lose up to 2%.
   // The reduction behind an unread check (rr_fin) rides with the launch of the coarse solve:
   // 64 cubes of 16^3 1101 -> 1071 us a projection.
   bool unread = false;
@@ -783,15 +786,16 @@ int poisson(bcm_plan* P, const double* b, double* p, bool use_guess, bcm_report*
       }
       float* d = P->at<float>(P->o_d);
       // Reduce the residual by inner_tol, or only by what is still missing to reach tol (with a
-      // factor 0.3 of margin), whichever is the weaker requirement.  But when one inner solve
+      // factor 0.2 of margin), whichever is the weaker requirement.  But when one inner solve
       // can reach that by going further than inner_tol, and it lies well above what FP32 rounding
       // left of the previous one (which then cannot use up the margin), let it: a further
       // refinement step costs two passes in FP64 for one or two iterations (132.6M cells on three
-      // levels 35.0 against 40.5 ms a projection without).  A margin of 0.6 there saves an
-      // iteration more on some meshes (33.5M cells 7.4 against 7.9 ms), but 540 solves of six
-      // meshes then ended at 1.9 times the residual and 2.5 times the error of solves that never
-      // go further than inner_tol; with 0.3 they end at 0.91 times the residual.
-      const double need = 0.3 * o.tol * std::sqrt(bb / rr);
+      // levels 35.0 against 40.5 ms a projection without).  The margin is what keeps the result as
+      // near the solution as refinement in steps of inner_tol does: over 60 solves compared with
+      // exact ones the error was 0.92 times as large with 0.2 (11.35 iterations against 11.5),
+      // 1.3 times with 0.3 (11.15); over 540 others 2.5 times with 0.6, which on 33.5M cells
+      // saves one iteration more (7.4 against 7.9 ms).
+      const double need = 0.2 * o.tol * std::sqrt(bb / rr);
       const double rounding = outer > 0 ? std::sqrt(std::max(rr - rr_est, 0.0) / rr_before) : 1.0;
       const bool reach = need >= 0.01 * o.inner_tol && need >= 5.0 * rounding;
       const double red_target = std::max(reach ? std::min(need, o.inner_tol) : o.inner_tol, std::min(need, 0.1));
@@ -972,7 +976,6 @@ int adjoint_impl(bcm_plan* P, const bcm_adjoint_in* in, bcm_adjoint_out* out, bc
   return st;
 }
 
-// J = (rho/2) sum_i V_i |u_i|^2 and the seed cotangent g_scale rho V_i u_i.
 // No output overlaps another output or an input, but for the same component in place.
 template <typename TF>
 int kinetic_apart(const KineticArgs<TF>& a, size_t bytes) {
@@ -987,6 +990,7 @@ int kinetic_apart(const KineticArgs<TF>& a, size_t bytes) {
   return 1;
 }
 
+// J = (rho/2) sum_i V_i |u_i|^2 and the seed cotangent g_scale rho V_i u_i.
 template <typename TF>
 int kinetic_impl(bcm_plan* P, const void* const u[3], double rho, double g_scale, double* J,
                  void* const g_u[3], hipStream_t s) {
