@@ -668,6 +668,14 @@ int residual64(bcm_plan* P, const double* p, const double* b, TO* r, double rsca
 // 1.11 after the second; 13 iterations without, 24 carrying both times, 15 the second alone).
 constexpr double kCarryMax = 1.05;
 
+// An inner solve that reduces the residual norm by this factor an iteration or more is fast.  After
+// others the direction is not carried and the next solve not asked for more than inner_tol: a weak
+// or unsymmetric V-cycle (no pre-smoothing, the capped CG on the coarsest level) takes flexible CG
+// into stagnation, which a restart ends and a carried direction prolongs.  The V-cycles that gain
+// by carrying reduce the norm by 0.07 to 0.21; of 600 solves with weak ones, at 0.3 to 0.7, two
+// stagnated for good when the direction was always carried.
+constexpr double kFastRate = 0.25;
+
 constexpr double kFp64Floor = 64 * 2.220446049250313e-16;  // relative residual FP64 can reach
 
 // Solve A p = b to opts.tol (relative, V-weighted, FP64).  p holds the guess if use_guess.
@@ -750,6 +758,7 @@ int poisson(bcm_plan* P, const double* b, double* p, bool use_guess, bcm_report*
     double rscale = 1.0, rr_prev = HUGE_VAL;
     double rr_before = 0.0, rr_est = 0.0;  // <r, r> before the last inner solve, its estimate after
     int slow = 0;  // consecutive refinement steps that did not halve the residual norm
+    bool fast = false;  // the last inner solve converged at kFastRate or faster
     for (outer = 0; outer < o.max_outer; ++outer) {
       float* r32 = P->at<float>(P->o_r);
       const double* pg = (use_guess || outer) ? p : nullptr;
@@ -786,25 +795,29 @@ int poisson(bcm_plan* P, const double* b, double* p, bool use_guess, bcm_report*
       }
       float* d = P->at<float>(P->o_d);
       // Reduce the residual by inner_tol, or only by what is still missing to reach tol (with a
-      // factor 0.2 of margin), whichever is the weaker requirement.  But when one inner solve
-      // can reach that by going further than inner_tol, and it lies well above what FP32 rounding
-      // left of the previous one (which then cannot use up the margin), let it: a further
-      // refinement step costs two passes in FP64 for one or two iterations (132.6M cells on three
-      // levels 35.0 against 40.5 ms a projection without).  The margin is what keeps the result as
-      // near the solution as refinement in steps of inner_tol does: over 60 solves compared with
-      // exact ones the error was 0.92 times as large with 0.2 (11.35 iterations against 11.5),
-      // 1.3 times with 0.3 (11.15); over 540 others 2.5 times with 0.6, which on 33.5M cells
-      // saves one iteration more (7.4 against 7.9 ms).
-      const double need = 0.2 * o.tol * std::sqrt(bb / rr);
-      const double rounding = outer > 0 ? std::sqrt(std::max(rr - rr_est, 0.0) / rr_before) : 1.0;
-      const bool reach = need >= 0.01 * o.inner_tol && need >= 5.0 * rounding;
+      // margin), whichever is the weaker requirement.  But when one inner solve can reach that by
+      // going further than inner_tol, converges fast, and FP32 rounding left so little of the
+      // previous one that it cannot use up the margin, let it: a further refinement step costs two
+      // passes in FP64 for one or two iterations.
+      // The margin, a factor 0.3, is 0.2 for a solve that carries a direction, which falls below
+      // its target by less.  It is what keeps the result as near the solution as refinement in
+      // steps of inner_tol does: over 60 solves compared with exact ones the error was 0.92 times
+      // as large so (11.35 iterations against 11.5), 1.3 times with 0.3 throughout (11.15); over
+      // 540 others 2.5 times with 0.6, which on 33.5M cells saves one iteration more (7.4 against
+      // 7.9 ms).  132.6M cells on three levels take 34.9 ms a projection, 40.4 without carrying.
+      const bool carry = o.krylov == 1 && fast && rr <= kCarryMax * rr_est;
+      const double need = (carry ? 0.2 : 0.3) * o.tol * std::sqrt(bb / rr);
+      const bool reach = fast && need >= 0.01 * o.inner_tol &&
+                         need >= 5.0 * std::sqrt(std::max(rr - rr_est, 0.0) / rr_before);
       const double red_target = std::max(reach ? std::min(need, o.inner_tol) : o.inner_tol, std::min(need, 0.1));
       rr_before = rr;
       const double thr = red_target * red_target * rr * rscale * rscale;
+      const int before = log.iters;
       UpdateArgs<float> last{};  // the inner solve's last x update, folded into kc_ir
       if ((st = krylov<float>(P, d, true, thr, o.max_iter, 1.0 / (rscale * std::sqrt(bb)), log, &hs, s,
-                              rr * rscale * rscale, &last, outer > 0 && rr <= kCarryMax * rr_est)))
+                              rr * rscale * rscale, &last, carry)))
         return fail(st);
+      fast = hs.rr <= rr * rscale * rscale * std::pow(kFastRate * kFastRate, log.iters - before);
       IrArgs<float> ia{geom(P, P->n), p, d, P->at<double>(P->o_pf), 1.0 / rscale, p_unwritten ? 1 : 0,
                        last.p, last.sc, last.p ? last.x_zero : 0};
       HIPCHK(timed(P, cls_of(P, "ir", 0), s, [&] { return launch_ir<float>(P->n, ia, s); }), "kc_ir");

@@ -7,7 +7,7 @@ refinement step after the first, which starts the next."""
 import pytest
 import torch
 
-from bcm_inputs import CHANNEL_BC, uniform_mesh
+from bcm_inputs import CHANNEL_BC, OPEN_BC, uniform_mesh
 
 from gpu_util import log, plan_for, requires_gpu
 
@@ -36,3 +36,22 @@ def test_carrying_does_not_cost_iterations(dims):
     for f, x in zip(count["fp64"], count["mixed"]):
         assert f.status == 0 and x.status == 0
         assert x.n_inner <= f.n_inner + x.n_outer - 1
+
+
+@pytest.mark.parametrize("seed,dims,n,opts", [
+    (403, (3, 1, 4), 16, dict(post_sweeps=2, inner_tol=1e-2)),
+    (507, (2, 2, 2), 16, dict(post_sweeps=3, inner_tol=1e-2)),
+    (153, (2, 1, 2), 16, dict(post_sweeps=2, inner_tol=1e-2))])
+def test_a_weak_v_cycle_converges_by_its_restarts(seed, dims, n, opts):
+    """Without pre-smoothing and with the capped coarse CG flexible CG stagnates inside inner solves;
+    a direction carried into the next one goes on stagnating, the restart does not."""
+    for bc in (OPEN_BC, CHANNEL_BC, ("outflow", "inflow", "slip", "outflow", "inflow", "slip")):
+        m = uniform_mesh(dims, 1.0, n, bc)
+        plan = plan_for(m, "mixed", coarse_solver=0, pre_sweeps=0, prolong=0, **opts)
+        for k in range(8):
+            gen = torch.Generator(device="cuda").manual_seed(seed + 1000 * k)
+            b = torch.randn(m.n_cells, generator=gen, device="cuda", dtype=torch.float64)
+            for rhs in (b, plan.apply_laplacian(b)):
+                _, rep = plan.poisson_solve(rhs)
+                log(f"  {bc[0]} {dims} {k}: status {rep.status}, {rep.n_outer} steps, {rep.n_inner} iterations")
+                assert rep.status == 0 and rep.final_rel_res <= 1e-10
