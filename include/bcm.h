@@ -114,9 +114,9 @@ typedef struct {
                            restarted from the true residual (both share max_iter)      [10] */
   double inner_tol;     /* mixed modes: residual reduction asked of each FP32 inner solve
                            (the last one as much as tol still needs: less, or up to 100
-                           times more where FP32 rounding leaves room for it); FP32
-                           rounding of the operator limits what one refinement step gains
-                                                                                   [1e-3] */
+                           times more where the solves converge fast and FP32 rounding
+                           leaves room for it); FP32 rounding of the operator limits what
+                           one refinement step gains                             [1e-3] */
   int32_t pre_sweeps;   /* red-black Gauss-Seidel sweeps before restriction             [2] */
   int32_t post_sweeps;  /* sweeps after prolongation                                    [2] */
   int32_t coarse_iters; /* CG iterations on the one-cell-per-cube level (coarse_solver 0),

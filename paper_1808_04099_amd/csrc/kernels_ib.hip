@@ -139,7 +139,7 @@ __global__ void k_zero_u32(unsigned int* p) { *p = 0u; }
 
 // u* = u~ for the three components in one launch, 16 bytes a lane, four loads in flight, past the
 // caches (each value is touched once), and the skip counter to zero.  Bound by memory: 3 x 33.5M
-// FP64 values in 269 us, 6.0 TB/s (three device-to-device copies: about 310 us; the whole call,
+// FP64 values in 258 us, 6.2 TB/s (three device-to-device copies: about 310 us; the whole call,
 // with the counter read through the pinned mirror instead of a copy and a stream
 // synchronisation, 377 -> 320 us; 512 or 2048 workgroups a field: 337 and 328 us).
 __global__ __launch_bounds__(256) void k_ib_copy(IbCopyArgs a) {

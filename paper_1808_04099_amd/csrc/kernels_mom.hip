@@ -24,7 +24,7 @@
 //
 // What bounds it: HBM, with what two waves a SIMD keep in flight.  A Crank-Nicolson sweep of
 // 33.5M cells in FP64 takes 0.81 ms and moves 4.0 GB (96 bytes per cell are 3.2 GB; the rest is
-// halo rows, planes and the face buffers), 4.9 TB/s; the VALU is busy 44% of it.  With every
+// halo rows, planes and the face buffers), 4.9 TB/s; the VALU is busy 43% of it.  With every
 // neighbour through LDS, two barriers a plane and nothing loaded ahead it took 1.00 ms, and a
 // separate export pass 0.2 ms a step.  About 250 registers: three waves a SIMD spill 90 of them
 // and take three times as long; reading the y neighbours from memory instead of LDS keeps the L1
